@@ -110,8 +110,8 @@ def _register_workspace():
         ff.ffuse_set_workspace(_workspace)
 
 
-def prepare(case, seed):
-    _register_workspace()
+def _tensors(case, seed):
+    """The operands of a case in the order of its call (X, W1, W3 or None, W2), from the seed alone."""
     dt = _TORCH[case["dtype"]]
     gen = torch.Generator(device="cuda").manual_seed(seed)
 
@@ -121,22 +121,23 @@ def prepare(case, seed):
             return t.uniform_(-scale, scale, generator=gen)
         return t.normal_(0.0, scale, generator=gen)
 
-    s = {"kind": case["kind"], "act": _ACTS[case["act"]]}
     if case["kind"] == "conv":
         B, H, W, IC, OC1, OC2, k = (case[n] for n in ("B", "H", "W", "IC", "OC1", "OC2", "k1"))
-        s["call"] = _CONV[case["dtype"]]
-        s["X"] = tensor((B, H, W, IC), 1.0)
-        s["W1"] = tensor((k, k, IC, OC1), (k * k * IC) ** -0.5)
-        s["W2"] = tensor((1, 1, OC1, OC2), OC1 ** -0.5)
-        s["Y"] = torch.empty((B, H, W, OC2), dtype=dt, device="cuda")
-        return s
+        return (tensor((B, H, W, IC), 1.0), tensor((k, k, IC, OC1), (k * k * IC) ** -0.5), None,
+                tensor((1, 1, OC1, OC2), OC1 ** -0.5))
     M, K, N1, N2 = (case[n] for n in ("M", "K", "N1", "N2"))
-    s["call"] = _CALL[case["dtype"]]
-    s["X"] = tensor((M, K), 1.0)
-    s["W1"] = tensor((K, N1), K ** -0.5)
-    s["W3"] = tensor((K, N1), K ** -0.5) if case["gated"] else None
-    s["W2"] = tensor((N1, N2), N1 ** -0.5)
-    s["Y"] = torch.empty((M, N2), dtype=dt, device="cuda")
+    X, W1 = tensor((M, K), 1.0), tensor((K, N1), K ** -0.5)
+    W3 = tensor((K, N1), K ** -0.5) if case["gated"] else None
+    return X, W1, W3, tensor((N1, N2), N1 ** -0.5)
+
+
+def prepare(case, seed):
+    _register_workspace()
+    s = {"kind": case["kind"], "act": _ACTS[case["act"]]}
+    s["call"] = (_CONV if case["kind"] == "conv" else _CALL)[case["dtype"]]
+    s["X"], s["W1"], s["W3"], s["W2"] = _tensors(case, seed)
+    shape = (case["B"], case["H"], case["W"], case["OC2"]) if case["kind"] == "conv" else (case["M"], case["N2"])
+    s["Y"] = torch.empty(shape, dtype=_TORCH[case["dtype"]], device="cuda")
     return s
 
 
@@ -167,3 +168,22 @@ _TOLERANCE = {"bf16": {"rel": 1e-2, "max": 0.05}, "f16": {"rel": 1.2e-3, "max": 
 
 def tolerance(case):
     return dict(_TOLERANCE[case["dtype"]])
+
+
+_EXACT_ACT = {"relu": torch.relu, "gelu": lambda v: torch.nn.functional.gelu(v, approximate="tanh"),
+              "silu": torch.nn.functional.silu}
+
+
+def exact(case, seed):
+    """The chain in 64 bits, with nothing rounded between its products."""
+    X, W1, W3, W2 = (None if t is None else t.double() for t in _tensors(case, seed))
+    act = _EXACT_ACT[case["act"]]
+    if case["kind"] == "ffn":
+        h = act(X @ W1)
+        if W3 is not None:
+            h *= X @ W3
+        return h @ W2
+    k, H, W = case["k1"], case["H"], case["W"]
+    padded = torch.nn.functional.pad(X, (0, 0, k // 2, k // 2, k // 2, k // 2))
+    h = sum(padded[:, i:i + H, j:j + W].reshape(-1, case["IC"]) @ W1[i, j] for i in range(k) for j in range(k))
+    return (act(h) @ W2[0, 0]).reshape(case["B"], H, W, case["OC2"])
