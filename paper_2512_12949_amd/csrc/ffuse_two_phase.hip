@@ -80,6 +80,18 @@ template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 128, false, 128
     static constexpr bool DEEP = true;
     static constexpr bool PREFETCH = true;
 };
+// 256-column slices: the wave tile of the second phase (64 x 128) in the first one as well.  With 128 x 128
+// items a wave reads 2 fragments per MFMA pair and the phase is bound by LDS reads (0.36 of the MFMA peak);
+// 64 x 128 wave tiles sustain 0.46.  512 x 4096 x 16384 x 4096: 256 items, one full round instead of two,
+// 163 -> 145 us.  (Gated 128-column slices already are this tile.)
+template <typename T> struct TwoPhaseGemms<T, false, 128, false, 256, true> {
+    static constexpr int BH1 = 256;
+    template <bool NT> using G1 = WideGemm<T, false, 128, 256, 2, 2, 4, NT>;
+    template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, 2, 4, NT>;
+    static constexpr bool HAS_NT = true;
+    static constexpr bool DEEP = true;
+    static constexpr bool PREFETCH = true;
+};
 template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 128, false, 64, true> {
     static constexpr int BH1 = 64;
     template <bool NT> using G1 = WideGemm<T, GATED, 128, 64, 2, 2, 8, NT>;
@@ -467,6 +479,8 @@ template <typename T, bool GATED> static const void* two_phase_fn(int bm, int bh
         if (bm == 64) return (const void*)fused_two_phase_kernel<T, GATED, 64, false, 64, true>;
         if (bm == 128) return (const void*)fused_two_phase_kernel<T, GATED, 128, false, 64, true>;
     }
+    if constexpr (!GATED)
+        if (bk == 32 && bm == 128 && bh1 == 256) return (const void*)fused_two_phase_kernel<T, false, 128, false, 256, true>;
     if (bk == 32 && bm != 256) return nullptr;
     if (bm == 32 && bh1 == 128) return (const void*)fused_two_phase_kernel<T, GATED, 32>;
     if (bm == 64 && bh1 == 128) return (const void*)fused_two_phase_kernel<T, GATED, 64>;

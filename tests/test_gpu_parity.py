@@ -147,6 +147,22 @@ def test_two_phase_narrow_hidden_slices(dtype, gated):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_two_phase_wide_slices_in_128_row_blocks(dtype):
+    """128 x 256 first-phase tiles: one ragged tile, a ragged second slice and row block, more items than
+    workgroups; K shorter and longer than the ring; direct output and partial planes; the weight-load hint
+    is a template twin and rides along through the environment elsewhere."""
+    for (M, K, N1, N2) in [(100, 40, 248, 264), (300, 200, 840, 264), (520, 328, 16904, 72)]:
+        w, host, dev = _case("wide", M, K, N1, N2, dtype, ACT_GELU_TANH, False)
+        rows = inputs.sample_rows(M, 128, 24, seed=3)
+        ref = gu.oracle_rows(w, host, rows)
+        for splits, raster in ((1, 2), (3, 4)):
+            plan = ff.make_plan(ff.FAMILY_TWOPHASE, bm=128, bh=256, bk=32, splits=splits, raster=raster)
+            what = f"wide slices {dtype} {(M, K, N1, N2)} splits={splits}"
+            print(what, flush=True)
+            gu.check(gu.run(w, dev, plan=plan), ref, dtype, rows=rows, what=what)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("gated", [False, True])
 def test_two_phase_non_temporal_weight_streaming(dtype, gated, monkeypatch):
     """The instantiations that stream the weights with the non-temporal hint (chosen by the
