@@ -1,7 +1,13 @@
-// fp32 debug path: the same chain on plain FMA (no matrix cores), for checking the schedule
-// and the boundary at full precision.  Same "reduce" structure as the 16-bit fused kernel:
+// fp32 path: the same chain on the fp32 matrix instructions (full fp32 products and sums), for checking the
+// schedule and the boundary at full precision.  Same "reduce" structure as the 16-bit fused kernel:
 // one workgroup per (16-row block, 64-wide hidden slice), complete K sums before the
 // activation (paper Sec. 4.3, Rule 3), partial second products added atomically into Y.
+//
+// What bounds it: on the shapes it is for (up to a few hundred rows and widths) the latency of one workgroup.
+// So every operand goes straight from global memory to the registers of the wave that multiplies it, with many
+// loads in flight together and no barrier between them: the four waves split K (partial tiles summed in LDS), a
+// W1 row is read as 16 lanes x 16 bytes that feed four column tiles, and the second product's first weights are on
+// their way while the first product is summed.
 #include "ffuse_dev.h"
 #include "ffuse_launch.h"
 #include <mutex>
@@ -23,88 +29,141 @@ static __device__ __forceinline__ float act_f32(int act, float x) {
     }
 }
 
-constexpr int F_BM = 16, F_BH = 64, F_BK = 32;
+constexpr int F_BM = 16, F_BH = 64;
+constexpr int F_HLD = F_BH + 4;   // row stride of the H block in LDS (floats)
 
-// H block [16][64] of act(X W1) [.* X W3] for rows m0.., hidden n0.. into hs (LDS).
+// v_mfma_f32_16x16x4_f32: lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and D[4 * (l / 16) + r][l % 16].
+// A group of 16 k is multiplied by four of them: instruction j takes k = 4 * (l / 16) + j, so that a lane's four
+// k of A are 16 consecutive bytes.  Column tile i of the four that a wave computes side by side holds the columns
+// 4 * (l % 16) + i, so that a lane's four columns of B are 16 consecutive bytes too.
+__device__ __forceinline__ void mma_group_f32(const f32x4& x, const f32x4 (&w)[4], f32x4 (&acc)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], w[j][i], acc[i], 0, 0, 0);
+}
+// the 16-byte units of rows k0 + 4 * (lane / 16) + 0..3 of a [K][N] matrix at this lane's columns
+__device__ __forceinline__ void load_rows_f32(__amdgpu_buffer_rsrc_t r, int k, uint32_t row_bytes, uint32_t col_bytes, bool ok, f32x4 (&w)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        w[j] = __builtin_bit_cast(f32x4, buf_load16(r, ok ? (uint32_t)(k + j) * row_bytes + col_bytes : kOob));
+}
+
+// H block [16][64] of act(X W1) [.* X W3] for rows m0.., hidden n0.. into hs (LDS).  part: a partial tile a wave
+// (and branch).  Ends with a barrier.  The groups of 16 k are dealt to the waves in turn, BATCH at a time each:
+// 64 registers of operands in flight (K <= 256: all of a wave's loads are issued at once).  Rows past M, k past K
+// and columns past N1 read as zeros (K, N1 and N2 are multiples of 8).
+template <bool GATED>
 static __device__ __forceinline__ void first_product_f32(const float* X, const float* W1, const float* W3,
                                                          int64_t M, int K, int N1, int act, int64_t m0, int n0,
-                                                         float (*xs)[F_BK + 1], float (*ws)[F_BH], float (*w3s)[F_BH],
-                                                         float (*hs)[F_BH + 1]) {
-    const int tid = threadIdx.x;
-    const int c = tid & 63, r0 = tid >> 6;  // column, first of 4 rows (r0, r0+4, r0+8, r0+12)
-    float g[4] = {0, 0, 0, 0}, u[4] = {0, 0, 0, 0};
-    for (int k0 = 0; k0 < K; k0 += F_BK) {
-        for (int i = tid; i < F_BM * F_BK; i += 256) {
-            const int r = i / F_BK, k = i % F_BK;
-            xs[r][k] = (m0 + r < M && k0 + k < K) ? X[(m0 + r) * K + k0 + k] : 0.0f;
-        }
-        for (int i = tid; i < F_BK * F_BH; i += 256) {
-            const int k = i / F_BH, n = i % F_BH;
-            const bool ok = (k0 + k < K) && (n0 + n < N1);
-            ws[k][n] = ok ? W1[(int64_t)(k0 + k) * N1 + n0 + n] : 0.0f;
-            if (W3) w3s[k][n] = ok ? W3[(int64_t)(k0 + k) * N1 + n0 + n] : 0.0f;
-        }
-        __syncthreads();
-        for (int k = 0; k < F_BK; ++k) {
-            const float w = ws[k][c];
-            const float w3 = W3 ? w3s[k][c] : 0.0f;
+                                                         float (*part)[F_BM][F_BH], float (*hs)[F_HLD]) {
+    constexpr int G = GATED ? 2 : 1, BATCH = GATED ? 2 : 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(X, (uint32_t)((uint64_t)M * K * 4));
+    const __amdgpu_buffer_rsrc_t rw[2] = {make_rsrc(W1, (uint32_t)((uint64_t)K * N1 * 4)),
+                                          make_rsrc(GATED ? W3 : W1, (uint32_t)((uint64_t)K * N1 * 4))};
+    const uint32_t xrow = (uint32_t)(m0 + c) * (uint32_t)K * 4u, wrow = (uint32_t)N1 * 4u;
+    const int col = n0 + 4 * c;
+    f32x4 acc[G][4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float xv = xs[r0 + 4 * q][k];
-                g[q] = fmaf(xv, w, g[q]);
-                u[q] = fmaf(xv, w3, u[q]);
-            }
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[g][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int g0 = 0; g0 * 16 < K; g0 += 4 * BATCH) {
+        f32x4 x[BATCH], w[BATCH][G][4];
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) {
+            const int k = 16 * (g0 + 4 * b + wave) + 4 * q;
+            x[b] = __builtin_bit_cast(f32x4, buf_load16(rx, k < K ? xrow + 4u * (uint32_t)k : kOob));
+#pragma unroll
+            for (int g = 0; g < G; ++g) load_rows_f32(rw[g], k, wrow, 4u * (uint32_t)col, k < K && col < N1, w[b][g]);
         }
-        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b)
+#pragma unroll
+            for (int g = 0; g < G; ++g) mma_group_f32(x[b], w[b][g], acc[g]);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        float v = act_f32(act, g[q]);
-        if (W3) v *= u[q];
-        hs[r0 + 4 * q][c] = v;
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<f32x4*>(&part[4 * g + wave][4 * q + r][4 * c]) = f32x4{acc[g][0][r], acc[g][1][r], acc[g][2][r], acc[g][3][r]};
+    __syncthreads();
+    {
+        const int row = tid >> 4, cc = 4 * (tid & 15);
+        f32x4 v[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            v[g] = *reinterpret_cast<const f32x4*>(&part[4 * g][row][cc]);
+#pragma unroll
+            for (int p = 1; p < 4; ++p) v[g] += *reinterpret_cast<const f32x4*>(&part[4 * g + p][row][cc]);
+        }
+        f32x4 h;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            h[i] = act_f32(act, v[0][i]);
+            if constexpr (GATED) h[i] *= v[G - 1][i];
+            if (n0 + cc >= N1) h[i] = 0.0f;   // (an infinity of X times the zero weights past N1 is not a number)
+        }
+        *reinterpret_cast<f32x4*>(&hs[row][cc]) = h;
     }
     __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void fused_f32_kernel(FusedArgs a, float* Y) {
-    __shared__ float xs[F_BM][F_BK + 1];
-    __shared__ float ws[F_BK][F_BH];
-    __shared__ float w3s[F_BK][F_BH];
-    __shared__ float hs[F_BM][F_BH + 1];
-    const float* X = (const float*)a.X;
-    const float* W1 = (const float*)a.W1;
-    const float* W3 = (const float*)a.W3;
-    const float* W2 = (const float*)a.W2;
+template <bool GATED> __global__ __launch_bounds__(256) void fused_f32_kernel(FusedArgs a, float* Y) {
+    __shared__ __attribute__((aligned(16))) float part[GATED ? 8 : 4][F_BM][F_BH];
+    __shared__ __attribute__((aligned(16))) float hs[F_BM][F_HLD];
     const int64_t m0 = (int64_t)blockIdx.x * F_BM;
     const int n0 = blockIdx.y * F_BH;
-    first_product_f32(X, W1, W3, a.M, a.K, a.N1, a.act, m0, n0, xs, ws, w3s, hs);
-    const int nvalid = min(F_BH, a.N1 - n0);
-    for (int j = threadIdx.x; j < a.N2; j += 256) {
-        float acc[F_BM];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    // the wave's blocks of 64 output columns: wave, wave + 4, ...; rows of W2 past N1 lie past the buffer (zeros)
+    const __amdgpu_buffer_rsrc_t r2 = make_rsrc(a.W2, (uint32_t)((uint64_t)a.N1 * a.N2 * 4));
+    const uint32_t w2row = (uint32_t)a.N2 * 4u;
+    f32x4 w[4][4];
+    const auto load2 = [&](int cb) {
+        const int col = 64 * cb + 4 * c;
 #pragma unroll
-        for (int r = 0; r < F_BM; ++r) acc[r] = 0.0f;
-        for (int n = 0; n < nvalid; ++n) {
-            const float w = W2[(int64_t)(n0 + n) * a.N2 + j];
+        for (int t = 0; t < 4; ++t) load_rows_f32(r2, n0 + 16 * t + 4 * q, w2row, 4u * (uint32_t)col, col < a.N2, w[t]);
+    };
+    load2(wave);
+    first_product_f32<GATED>((const float*)a.X, (const float*)a.W1, (const float*)a.W3, a.M, a.K, a.N1, a.act, m0, n0, part, hs);
+    f32x4 h[4];
 #pragma unroll
-            for (int r = 0; r < F_BM; ++r) acc[r] = fmaf(hs[r][n], w, acc[r]);
-        }
+    for (int t = 0; t < 4; ++t) h[t] = *reinterpret_cast<const f32x4*>(&hs[c][16 * t + 4 * q]);
+    for (int cb = wave; 64 * cb < a.N2; cb += 4) {
+        f32x4 acc[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mma_group_f32(h[t], w[t], acc);
+        if (64 * (cb + 4) < a.N2) load2(cb + 4);
+        // through the wave's own partial tile, so that the 64 lanes of an atomic add cover 256 consecutive bytes
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<f32x4*>(&part[wave][4 * q + r][4 * c]) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int col = 64 * cb + lane;
 #pragma unroll
         for (int r = 0; r < F_BM; ++r)
-            if (m0 + r < a.M)
-                __hip_atomic_fetch_add(Y + (m0 + r) * a.N2 + j, acc[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (m0 + r < a.M && col < a.N2)
+                __hip_atomic_fetch_add(Y + (m0 + r) * a.N2 + col, part[wave][r][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();   // the tile is read before the next block's is written
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 }
 
 // C = act(A B) [.* A B3], fp32, 16 x 64 tile per workgroup
-__global__ __launch_bounds__(256) void gemm_act_f32_kernel(GemmArgs a) {
-    __shared__ float xs[F_BM][F_BK + 1];
-    __shared__ float ws[F_BK][F_BH];
-    __shared__ float w3s[F_BK][F_BH];
-    __shared__ float hs[F_BM][F_BH + 1];
+template <bool GATED> __global__ __launch_bounds__(256) void gemm_act_f32_kernel(GemmArgs a) {
+    __shared__ __attribute__((aligned(16))) float part[GATED ? 8 : 4][F_BM][F_BH];
+    __shared__ __attribute__((aligned(16))) float hs[F_BM][F_HLD];
     const int64_t m0 = (int64_t)blockIdx.x * F_BM;
     const int n0 = blockIdx.y * F_BH;
-    first_product_f32((const float*)a.A, (const float*)a.B, (const float*)a.B3, a.M, a.K, a.N, a.act, m0, n0, xs, ws,
-                      w3s, hs);
+    first_product_f32<GATED>((const float*)a.A, (const float*)a.B, (const float*)a.B3, a.M, a.K, a.N, a.act, m0, n0, part, hs);
     float* C = (float*)a.C;
     for (int i = threadIdx.x; i < F_BM * F_BH; i += 256) {
         const int r = i / F_BH, c = i % F_BH;
@@ -158,13 +217,15 @@ hipError_t launch_fused_f32(const FusedArgs& a, float* Y, hipStream_t st) {
     hipError_t e = launch_zero(Y, sizeof(float) * (size_t)a.M * a.N2, st);
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)((a.M + F_BM - 1) / F_BM), (unsigned)((a.N1 + F_BH - 1) / F_BH));
-    hipLaunchKernelGGL(fused_f32_kernel, grid, dim3(256), 0, st, a, Y);
+    if (a.W3) hipLaunchKernelGGL(fused_f32_kernel<true>, grid, dim3(256), 0, st, a, Y);
+    else hipLaunchKernelGGL(fused_f32_kernel<false>, grid, dim3(256), 0, st, a, Y);
     return hipGetLastError();
 }
 
 hipError_t launch_gemm_act_f32(const GemmArgs& a, hipStream_t st) {
     dim3 grid((unsigned)((a.M + F_BM - 1) / F_BM), (unsigned)((a.N + F_BH - 1) / F_BH));
-    hipLaunchKernelGGL(gemm_act_f32_kernel, grid, dim3(256), 0, st, a);
+    if (a.B3) hipLaunchKernelGGL(gemm_act_f32_kernel<true>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(gemm_act_f32_kernel<false>, grid, dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -40,6 +40,35 @@ def test_fp32_ragged(act, gated):
     gu.check(gu.run(w, dev, unfused=True), ref, "f32", what="f32 unfused")
 
 
+@pytest.mark.parametrize("gated", [False, True])
+def test_fp32_tile_edges(gated):
+    """One short group of k, one row, one unit of columns; K on and beside a wave's batch of groups (64, 128, 256);
+    more output blocks of 64 columns than waves; the last hidden slice of 8 columns.  fp32 rounding bounds the
+    error: K + N1 products and sums of relative error 2^-24 each, growing like the square root of their number."""
+    for (M, K, N1, N2) in [(1, 8, 8, 8), (16, 64, 64, 64), (17, 136, 72, 264), (33, 256, 264, 328), (130, 520, 200, 72)]:
+        w, host, dev = _case("f32e", M, K, N1, N2, "f32", ACT_SILU if gated else ACT_GELU_TANH, gated)
+        ref = gu.oracle_rows(w, host)
+        print("f32 tiles", (M, K, N1, N2), gated, flush=True)
+        err = gu.check(gu.run(w, dev), ref, "f32", what="f32 fused")
+        assert err < 8 * 2.0 ** -24 * (K + N1) ** 0.5, err
+        gu.check(gu.run(w, dev, unfused=True), ref, "f32", what="f32 unfused")
+
+
+def test_fp32_infinite_rows_stay_in_their_rows():
+    """An infinity in X reaches its own output row only, and through the last, partly filled hidden slice as an
+    infinity or a NaN of the chain itself: relu(+inf) times weights of one sign is an infinity, not a NaN."""
+    w, host, dev = _case("f32i", 20, 16, 72, 72, "f32", ACT_RELU, False)
+    clean = gu.run(w, dev)
+    for name in ("W1", "W2"):
+        dev[name].abs_()
+    clean = gu.run(w, dev).clone()
+    dev["X"][3, 5] = float("inf")
+    y = gu.run(w, dev)
+    assert bool((y[3] == float("inf")).all())
+    keep = [r for r in range(20) if r != 3]
+    assert bool((y[keep] - clean[keep]).abs().max() <= 1e-5 * clean.abs().max())
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("gated", [False, True])
 def test_every_reduce_tile_on_a_ragged_shape(dtype, gated):
