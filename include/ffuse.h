@@ -86,12 +86,15 @@ typedef enum {
     FFUSE_FAMILY_AUTO = 0,
     FFUSE_FAMILY_REDUCE = 1,  /* hidden dimension split across workgroups; each keeps its
                                  activated slice on chip and the partial second products are
-                                 summed with fp32 atomics (Sec. 4.1 "reduce" strategy)      */
+                                 summed with fp32 atomics (Sec. 4.1 "reduce" strategy).
+                                 bm = 16 or 32 (bh = 64): operands straight to registers, `splits`
+                                 ranges of the hidden dimension summed as fp32 planes in a fixed
+                                 order; one range stores Y itself                             */
     FFUSE_FAMILY_EXCHANGE = 2,/* cooperating workgroups publish activated tiles to an
                                  L2-resident buffer and consume each other's tiles
                                  (Sec. 4.1 "shuffle" strategy, exchange through L2)         */
     FFUSE_FAMILY_UNFUSED = 3, /* traffic model only: two GEMM launches of 256-row tiles       */
-    FFUSE_FAMILY_SCALAR = 4,  /* fp32 debug kernels (plain FMA, no matrix cores)            */
+    FFUSE_FAMILY_SCALAR = 4,  /* fp32 kernels (fp32 matrix instructions, fp32 sums)         */
     FFUSE_FAMILY_ROWS = 6,    /* row-stationary: a workgroup owns bm = 64 rows and ALL N2 output columns
                                  (N2 <= 1024), keeps its rows of X in registers (K <= 1024), the output
                                  block in accumulators and one activated chunk of bh = 64 hidden columns in

@@ -184,11 +184,22 @@ ffuse_plan_t lookup_plan(int dtype, int act, int gated, int64_t M, int64_t K, in
         return it->second.plan;
     const auto key = table_key(dtype + 64 * g.objective, gated, K, N1, N2, -M);   // (modelled plans: one slot per objective)
     it = g.table.find(key);
-    if (it != g.table.end()) return it->second.plan;
     ffuse_plan_t plan;
-    ffuse::choose_plan(dtype, act, gated, M, K, N1, N2, &plan, g.objective);
+    if (it != g.table.end()) {
+        plan = it->second.plan;
+    } else {
+        ffuse::choose_plan(dtype, act, gated, M, K, N1, N2, &plan, g.objective);
+        if (g.table.size() > 4096) g.table.clear();
+        g.table[key] = {plan, 0.0};
+    }
+    if (!ffuse::is_direct(plan) || ffuse::plan_workspace_bytes(plan, dtype, gated, M, K, N1, N2) <= ws_bytes) return plan;
+    // the planes of the small row blocks want more than this workspace holds: the best of the other plans
+    const auto other = table_key(dtype + 256 + 64 * g.objective, gated, K, N1, N2, -M);
+    it = g.table.find(other);
+    if (it != g.table.end()) return it->second.plan;
+    ffuse::choose_plan(dtype, act, gated, M, K, N1, N2, &plan, g.objective, false);
     if (g.table.size() > 4096) g.table.clear();
-    g.table[key] = {plan, 0.0};
+    g.table[other] = {plan, 0.0};
     return plan;
 }
 
@@ -366,6 +377,23 @@ int run_plan(const ffuse_plan_t& plan, int dtype, const void* X, const void* W1,
         return FFUSE_OK;
     }
     if (plan.family != FFUSE_FAMILY_REDUCE) return FFUSE_ERR_PLAN;
+    if (ffuse::is_direct(plan)) {
+        ffuse::DirectGeometry dg;
+        if (!ffuse::direct_geometry(plan, M, N1, N2, &dg)) return FFUSE_ERR_PLAN;
+        if (!w.ptr || w.bytes < dg.ws_bytes) return FFUSE_ERR_WORKSPACE;
+        if (dg.ranges > 1) {
+            w.zero = 0;      // planes overwrite the region the larger tiles keep at zero, and maybe the two-phase family's flags
+            if (reinterpret_cast<char*>(w.small_flags) < reinterpret_cast<char*>(w.ptr) + dg.ws_bytes) w.small_flags = nullptr;
+        }
+        ffuse::DirectArgs d{X, W1, W3, W2, Y, reinterpret_cast<float*>(w.ptr), M, (int)K, (int)N1, (int)N2, act,
+                            dg.ranges, dg.slices, conv.ic, conv.h, conv.w};
+        g.exch_err = nullptr;
+        Timer t(st);
+        if (ffuse::launch_fused_direct(dtype, d, dg.bm, dg.ng, st) != hipSuccess) return FFUSE_ERR_LAUNCH;
+        t.stop();
+        g.last_plan = plan;
+        return FFUSE_OK;
+    }
     const size_t need = sizeof(float) * (size_t)M * (size_t)N2;
     if (!w.ptr || w.bytes < need) return FFUSE_ERR_WORKSPACE;
     if (!ensure_zero(w, need, st)) return FFUSE_ERR_LAUNCH;
@@ -736,6 +764,10 @@ int run_conv_chain(int dtype, const void* X, const void* W1, const void* W2, int
         if (plan.bh != 64 && plan.bh != 32) plan.bh = 128;
         found = plan.bm <= 128 && ffuse::plan_valid(plan, dtype, 0, M, K, OC1, OC2);
         if (!found) return FFUSE_ERR_PLAN;
+    } else if (g.forced && ffuse::is_direct(g.forced_plan)) {
+        plan = g.forced_plan;
+        if (!ffuse::plan_valid(plan, dtype, 0, M, K, OC1, OC2)) return FFUSE_ERR_PLAN;
+        found = true;
     } else {
         // the model's best plan among those the 3x3 loader's kernels implement: ranked once per shape, then
         // looked up (its own key space in the plan table: dtype + 32)
@@ -748,7 +780,7 @@ int run_conv_chain(int dtype, const void* X, const void* W1, const void* W2, int
             std::vector<ffuse::RankedPlan> ranked;
             ffuse::rank_plans(dtype, act, 0, M, K, OC1, OC2, &ranked);
             for (const auto& r : ranked)
-                if (r.plan.family == FFUSE_FAMILY_TWOPHASE && r.plan.bm <= 128 && r.plan.bk != 32 &&
+                if (((r.plan.family == FFUSE_FAMILY_TWOPHASE && r.plan.bm <= 128 && r.plan.bk != 32) || ffuse::is_direct(r.plan)) &&
                     ffuse::plan_workspace_bytes(r.plan, dtype, 0, M, K, OC1, OC2) <= ws.bytes) {
                     plan = r.plan;
                     found = true;

@@ -7,7 +7,7 @@
 //     workgroups produce activated tiles into a ring buffer read through that XCD's L2, the
 //     others consume them into register-resident output tiles (Sec. 4.1 "shuffle" strategy
 //     with the XCD as the cluster and its L2 as the shared on-chip pool).
-//   (the two-phase family, the default, lives in ffuse_two_phase.hip)
+//   (the two-phase family lives in ffuse_two_phase.hip, the reduce family on 16- and 32-row blocks in ffuse_direct.hip)
 //   * finalize_kernel       -- fp32 sums -> Y in the operand type, workspace back to zero.
 //   (the 16-bit unfused comparison path is the two-phase kernel launched one phase at a time)
 #include "ffuse_gemm1.h"

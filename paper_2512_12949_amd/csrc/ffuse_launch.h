@@ -101,11 +101,29 @@ struct RowsArgs {
 static constexpr int kRowsRing = 4;    // 4 KB weight slots per wave (measured on 32768 x 1024 x 8192 x 1024: 3 slots 1182 us, 4 1056, 5 1079, 6 1077)
 static constexpr int kRowsLdsBytes = 4 * kRowsRing * 4096 + 12 * 4096 + 64 * 128;   // rings | partial tiles | H chunk
 
+// reduce family on 16- and 32-row blocks
+struct DirectArgs {
+    const void* X;
+    const void* W1;
+    const void* W3;   // nullptr: not gated
+    const void* W2;
+    void* Y;
+    float* part;      // ranges > 1: fp32 partial sums [ranges][M][N2], fully overwritten
+    int64_t M;
+    int K, N1, N2;
+    int act;
+    int ranges;       // ranges of the hidden dimension, one workgroup each per row block
+    int slices;       // slices of 64 hidden columns per range
+    int conv_ic, conv_h, conv_w;   // as in TwoPhaseArgs
+};
+
 // 16-bit paths (dtype 0 = bf16, 1 = fp16)
 // nks: 16-k steps of the first product per wave (K <= 64 nks); nt2: 32-column output tiles per wave (N2 <= 128 nt2)
 hipError_t launch_fused_rows(int dtype, const RowsArgs& a, int nks, int nt2, int grid, hipStream_t st);
 hipError_t launch_fused_two_phase(int dtype, const TwoPhaseArgs& a, int bm, int bh1, int bk, int grid, hipStream_t st);
 hipError_t launch_finalize_planes(int dtype, const float* part, void* Y, int64_t count, int planes, hipStream_t st);
+// bm: rows per workgroup (16 or 32); ng: blocks of 256 output columns (1, 2, and with 16 rows 4 and 8); sums the planes too
+hipError_t launch_fused_direct(int dtype, const DirectArgs& a, int bm, int ng, hipStream_t st);
 hipError_t launch_fused_exchange(int dtype, const ExchangeArgs& a, int wgs_per_group, hipStream_t st);
 hipError_t launch_fused_reduce(int dtype, const FusedArgs& a, int bm, int bh, hipStream_t st);
 hipError_t launch_finalize(int dtype, float* sums, void* Y, int64_t count, hipStream_t st);

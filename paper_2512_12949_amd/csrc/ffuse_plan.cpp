@@ -58,6 +58,10 @@ bool plan_valid(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t 
         case FFUSE_FAMILY_UNFUSED: return true;
         case FFUSE_FAMILY_REDUCE:
             if (dtype == FFUSE_DT_F32) return false;
+            if (is_direct(p)) {
+                DirectGeometry dg;
+                return direct_geometry(p, M, N1, N2, &dg);
+            }
             return fused_reduce_tile_ok(gated, p.bm, p.bh) && p.raster >= 1;
         case FFUSE_FAMILY_TWOPHASE: {
             if (dtype == FFUSE_DT_F32) return false;
@@ -104,6 +108,23 @@ bool rows_geometry(const ffuse_plan_t& p, int gated, int64_t M, int64_t K, int64
     if ((p.bm != 0 && p.bm != 64) || (p.bh != 0 && p.bh != 64)) return false;
     g->nks = K <= 512 ? 8 : 16;
     g->nt2 = N2 <= 512 ? 4 : 8;
+    return true;
+}
+
+bool direct_geometry(const ffuse_plan_t& p, int64_t M, int64_t N1, int64_t N2, DirectGeometry* g) {
+    if ((p.bm != 16 && p.bm != 32) || (p.bh != 0 && p.bh != 64) || M < 1 || N1 < 8 || N2 < 8) return false;
+    // the output block of a workgroup stays in registers: 32 x 512 fp32 are 64 per lane, 16 x 2048
+    // 128 (32 x 1024 spilled, and no shape was faster with it)
+    if (N2 > (p.bm == 16 ? 2048 : 512)) return false;
+    g->bm = p.bm;
+    g->ng = N2 <= 256 ? 1 : (N2 <= 512 ? 2 : (N2 <= 1024 ? 4 : 8));
+    const int ns = (int)((N1 + 63) / 64);
+    const int want = p.splits > 0 ? std::min(p.splits, ns) : std::min(ns, two_phase_max_splits(M, N2));
+    if (want > 32) return false;
+    g->slices = (ns + want - 1) / want;
+    g->ranges = (ns + g->slices - 1) / g->slices;
+    // (at least what the family's larger tiles ask for, so that no call is accepted or refused differently)
+    g->ws_bytes = ((size_t)4 * M * N2 * g->ranges + 255) & ~(size_t)255;
     return true;
 }
 
@@ -277,6 +298,41 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
     double padded = t->flops, waves = 1.0;
     t->feasible = 1;
 
+    if (is_direct(p)) {
+        // Fitted on 33 shapes (1-32768 rows, K 8-4608, N2 8-2048), within about 15 % where the family is worth
+        // running.  A slice of 64 hidden columns costs two barriers and the issue of its loads: up to K = 256
+        // 0.9 us + 4 ns per k; beyond, 1.27 us per turn of the operand ring (512 k, gated 256) and 0.54 per block of
+        // 256 output columns.  32 rows take 1.33 times as long as 16.  Workgroups run one per CU; two of the smallest
+        // variant share one and then take 0.72 of twice the time.  Planes: their bytes, a second launch, eight at a time.
+        DirectGeometry dg;
+        t->feasible = direct_geometry(p, M, N1, N2, &dg) ? 1 : 0;
+        if (!t->feasible) return;
+        const double mb = cdiv(m, dg.bm), wgs = mb * dg.ranges, big = dg.bm == 32 ? 1.33 : 1.0;
+        const bool shortk = K <= 256 && dg.ng <= 2;
+        const double slice = 1e-6 * big * (shortk ? (0.9 + 0.004 * k) * (gated ? 1.3 : 1.0)
+                                                  : 0.5 + (gated ? 1.15 * cdiv(k, 256.0) : 1.27 * cdiv(k, 512.0)) + 0.54 * dg.ng);
+        double rounds = cdiv(wgs, d.cus);
+        if (shortk && dg.ng == 1 && rounds > 1.0) rounds *= 0.72;
+        const double weights = e * (g * k * n1 + n1 * n2), planes = dg.ranges > 1 ? 2.0 * 4.0 * m * n2 * dg.ranges : 0.0;
+        t->workgroups = (int)std::min(wgs, (double)d.cus);
+        t->l2_bytes = mb * weights + e * m * k * dg.ranges;
+        t->fabric_bytes = std::min(8.0, mb) * weights + e * m * k * std::min(8, dg.ranges) + e * m * n2 + planes;
+        t->reduce_bytes = planes;
+        t->hbm_bytes = t->q_min;
+        t->lds_used = (gated ? 8.0 : 4.0) * dg.bm * 256.0 + dg.bm * 144.0;
+        t->acc_regs = 4.0 * dg.ng * dg.bm;
+        t->t_hbm = t->hbm_bytes / d.hbm_bw;
+        t->t_fabric = t->fabric_bytes / d.fabric_bw;
+        t->t_l2 = t->l2_bytes / d.l2_bw;
+        t->t_mfma = rounds * dg.slices * slice;
+        t->t_reduce = dg.ranges > 1 ? planes / (0.5 * d.fabric_bw) + 2e-6 + 0.6e-6 * cdiv(dg.ranges, 8.0) : 0.0;
+        t->t_pred = 2.9e-6 + std::max({t->t_mfma, t->t_hbm, t->t_fabric}) + t->t_reduce;
+        // The two-phase prediction errs on the safe side where the two meet (measured 0.75-0.9 of it, gated 0.68-0.86:
+        // 200 x 1024 x 4096 x 1024 34 predicted and 28 measured, against 33 and 34 here; gated 16 x 1024 x 4096 x 1024
+        // 32 and 22, against 23 and 24), so this one is ranked with the same margin.
+        t->t_pred *= gated ? 1.45 : 1.2;
+        return;
+    }
     if (p.family == FFUSE_FAMILY_REDUCE) {
         const double bm = p.bm, bh = p.bh, R = std::max(1, p.raster);
         const double MB = cdiv(m, bm), S = cdiv(n1, bh), units = MB * S;
@@ -505,7 +561,7 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
 // Enumerates the plans the kernels implement, discards infeasible ones and ranks the rest by
 // predicted time (Sec. 4.3, Algorithm 2 up to the top-k list; the on-device profiling of that
 // list is ffuse_tune in the API layer).
-void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out) {
+void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out, bool direct) {
     (void)act;
     out->clear();
     ffuse_plan_t best;
@@ -516,6 +572,21 @@ void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1,
         best.splits = (int)((N1 + 63) / 64);
         out->push_back({0.0, best});
         return;
+    }
+    for (int bm = 16; direct && bm <= 32; bm += 16) {
+        const int ns = (int)((N1 + 63) / 64), most = std::min(ns, two_phase_max_splits(M, N2));
+        for (int sp = 1;; sp = std::min(2 * sp, most)) {
+            ffuse_plan_t p;
+            std::memset(&p, 0, sizeof(p));
+            p.family = FFUSE_FAMILY_REDUCE;
+            p.bm = bm; p.bh = 64; p.bn2 = 256; p.bk = 32; p.h_level = 1; p.raster = 1; p.splits = sp;
+            ffuse_traffic_t t;
+            if (plan_valid(p, dtype, gated, M, K, N1, N2)) {
+                traffic_model(p, dtype, gated, M, K, N1, N2, &t);
+                if (t.feasible) out->push_back({t.t_pred, p});
+            }
+            if (sp >= most) break;
+        }
     }
     static const int tiles[][2] = {{256, 256}, {128, 256}, {256, 128}, {128, 128}, {128, 64}};
     static const int rasters[] = {1, 2, 4, 8, 16};
@@ -606,9 +677,9 @@ void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1,
     std::stable_sort(out->begin(), out->end(), [](const RankedPlan& x, const RankedPlan& y) { return x.t_pred < y.t_pred; });
 }
 
-void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, ffuse_plan_t* out, int objective) {
+void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, ffuse_plan_t* out, int objective, bool direct) {
     std::vector<RankedPlan> r;
-    rank_plans(dtype, act, gated, M, K, N1, N2, &r);
+    rank_plans(dtype, act, gated, M, K, N1, N2, &r, direct);
     if (r.empty()) {
         std::memset(out, 0, sizeof(*out));
         return;
@@ -643,7 +714,12 @@ void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1
 size_t plan_workspace_bytes(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2) {
     (void)K;
     switch (p.family) {
-        case FFUSE_FAMILY_REDUCE: return sizeof(float) * (size_t)M * (size_t)N2;
+        case FFUSE_FAMILY_REDUCE:
+            if (is_direct(p)) {
+                DirectGeometry dg;
+                return direct_geometry(p, M, N1, N2, &dg) ? dg.ws_bytes : 0;
+            }
+            return sizeof(float) * (size_t)M * (size_t)N2;
         case FFUSE_FAMILY_EXCHANGE: {
             ExchangeGeometry e;
             return exchange_geometry(p, gated, M, N1, N2, kDevice.cus, &e) ? e.ws_bytes : 0;

@@ -68,6 +68,16 @@ struct RowsGeometry {
 };
 bool rows_geometry(const ffuse_plan_t& p, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, RowsGeometry* out);
 
+// Reduce family on row blocks of 16 or 32 rows: which kernel instantiation runs a plan, and how it splits.
+struct DirectGeometry {
+    int bm;              // 16 or 32
+    int ng;              // blocks of 256 output columns: 1 or 2, with 16 rows also 4 and 8
+    int ranges, slices;  // ranges of the hidden dimension (one workgroup each), slices of 64 columns per range
+    size_t ws_bytes;     // fp32 planes (one range stores none)
+};
+bool direct_geometry(const ffuse_plan_t& p, int64_t M, int64_t N1, int64_t N2, DirectGeometry* out);
+inline bool is_direct(const ffuse_plan_t& p) { return p.family == FFUSE_FAMILY_REDUCE && p.bm > 0 && p.bm <= 32; }
+
 bool fused_reduce_tile_ok(int gated, int bm, int bh);
 bool plan_valid(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2);
 void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2,
@@ -79,13 +89,13 @@ struct RankedPlan {
     double t_pred;
     ffuse_plan_t plan;
 };
-void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out);
+void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out, bool direct = true);   // direct: the 16- and 32-row reduce plans too
 // objective: FFUSE_OBJECTIVE_TIME -- the plan with the smallest predicted time; FFUSE_OBJECTIVE_BYTES -- among the
 // plans predicted within kBytesObjectiveSlack of that time, the one that moves the fewest bytes between the L2s
 // and the rest of the memory system
 constexpr double kBytesObjectiveSlack = 1.35;
 void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, ffuse_plan_t* out,
-                 int objective = FFUSE_OBJECTIVE_TIME);
+                 int objective = FFUSE_OBJECTIVE_TIME, bool direct = true);
 // Bytes of workspace a plan needs for this problem.
 size_t plan_workspace_bytes(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2);
 // The paper's bookkeeping of the search space (host arithmetic only; the chooser above enumerates the few

@@ -70,6 +70,24 @@ def test_ragged_3x3_chains(dtype, act):
             assert ff.ffuse_last_plan().bh == bh
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_3x3_chains_on_small_row_blocks(dtype):
+    """16- and 32-row reduce tiles: image edges inside a row block, several images, K of one and several turns of the ring."""
+    for i, (B, H, W, IC, OC1, OC2) in enumerate([(2, 5, 7, 64, 72, 40), (1, 1, 1, 64, 8, 8), (3, 9, 4, 128, 136, 264), (1, 3, 40, 192, 200, 1032)]):
+        w = inputs.ConvWorkload(f"d{i}", B, H, W, IC, OC1, OC2, 3, 1, dtype, ACT_RELU, 500 + i)
+        host = inputs.make_conv(w)
+        ref = oracle.conv_chain(host["X"], host["W1"], host["W2"], ACT_RELU, bf16=(dtype == "bf16"))
+        for bm in (16, 32):
+            if bm == 32 and OC2 > 512:
+                continue
+            for splits in sorted({1, 2, (OC1 + 63) // 64}):
+                plan = ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=splits)
+                what = f"{dtype} {(B, H, W, IC, OC1, OC2)} bm={bm} splits={splits}"
+                print(what, flush=True)
+                check(run_conv(w, host, plan), ref, dtype, what)
+                assert ff.ffuse_last_plan().bm == bm
+
+
 def test_pointwise_chain_and_argument_errors():
     w = inputs.ConvWorkload("p", 2, 6, 5, 72, 136, 40, 1, 1, "bf16", ACT_RELU, 410)
     host = inputs.make_conv(w)

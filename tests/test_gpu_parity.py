@@ -54,6 +54,60 @@ def test_fp32_tile_edges(gated):
         gu.check(gu.run(w, dev, unfused=True), ref, "f32", what="f32 unfused")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("gated", [False, True])
+def test_reduce_on_small_row_blocks(dtype, gated):
+    """16- and 32-row tiles: one short group of k, K on and beside a turn of the operand ring (128, 256, 512) and past
+    several, ragged rows, hidden widths and output widths, every count of output column blocks, one slice and several
+    per range, the last range shorter than the others; one range (stored directly) and planes."""
+    for (M, K, N1, N2) in [(1, 8, 8, 8), (16, 128, 64, 64), (33, 136, 200, 264), (50, 256, 328, 512), (17, 264, 136, 72),
+                           (40, 520, 192, 1000), (31, 1096, 72, 2048), (300, 72, 264, 320)]:
+        w, host, dev = _case("direct", M, K, N1, N2, dtype, ACT_SILU if gated else ACT_GELU_TANH, gated)
+        ref = gu.oracle_rows(w, host)
+        for bm in (16, 32):
+            for splits in sorted({1, 2, 3, (N1 + 63) // 64}):
+                plan = ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=splits)
+                what = f"small row blocks {dtype} gated={gated} {(M, K, N1, N2)} bm={bm} splits={splits}"
+                print(what, flush=True)
+                gu.Workspace.ensure(4 * M * N2 * splits + 256)
+                if bm == 32 and N2 > 512:
+                    with pytest.raises(ff.FfuseError):
+                        gu.run(w, dev, plan=plan)
+                    continue
+                gu.check(gu.run(w, dev, plan=plan), ref, dtype, what=what)
+
+
+def test_small_row_blocks_keep_infinities_in_their_rows():
+    """relu(+inf) through a last hidden slice of 8 columns: the row is infinite (weights of one sign), no other changes."""
+    w, host, dev = _case("directi", 20, 16, 72, 72, "bf16", ACT_RELU, False)
+    for name in ("W1", "W2"):
+        dev[name].abs_().clamp_(min=1e-3)
+    plan = ff.make_plan(ff.FAMILY_REDUCE, bm=16, bh=64, bk=32, splits=1)
+    clean = gu.run(w, dev, plan=plan)
+    dev["X"][3, 5] = float("inf")
+    y = gu.run(w, dev, plan=plan)
+    assert bool((y[3] == float("inf")).all())
+    keep = [r for r in range(20) if r != 3]
+    assert torch.equal(y[keep], clean[keep])
+
+
+def test_small_row_blocks_give_way_where_their_planes_do_not_fit():
+    """The model's choice for 128 x 384 x 1536 x 384 is 24 planes; a workspace that only holds another plan's still serves it."""
+    w, host, dev = _case("directw", 128, 384, 1536, 384, "bf16", ACT_GELU_TANH, False)
+    ref = gu.oracle_rows(w, host)
+    Y = torch.empty((128, 384), dtype=torch.bfloat16, device="cuda")
+    seen = []
+    for nbytes in (64 << 20, 4 << 20):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        Y.fill_(float("nan"))
+        ff.ffuse_ffn_ws(ff.DT_BF16, dev["X"], dev["W1"], None, dev["W2"], w.act, Y, ws)
+        torch.cuda.synchronize()
+        seen.append(ff.ffuse_last_plan().as_dict())
+        gu.check(Y, ref, "bf16", what=f"workspace of {nbytes}")
+    assert seen[0]["family"] == ff.FAMILY_REDUCE and seen[0]["bm"] == 16, seen
+    assert seen[1]["bm"] > 32, seen
+
+
 def test_fp32_infinite_rows_stay_in_their_rows():
     """An infinity in X reaches its own output row only, and through the last, partly filled hidden slice as an
     infinity or a NaN of the chain itself: relu(+inf) times weights of one sign is an infinity, not a NaN."""
