@@ -155,11 +155,36 @@ def _stream(stream):
     return ctypes.c_void_p(int(stream))
 
 
+# The layer calls below are what a serving loop issues back to back, and the smallest layers last no longer on the
+# device than a call takes here (7 us): plain integers instead of ctypes objects, and the stream's handle without a
+# Stream object around it.
+def _addr(t):
+    return None if t is None else t.data_ptr() if hasattr(t, "data_ptr") else int(t)
+
+
+_raw_stream = None
+
+
+def _stream_addr(stream):
+    if stream is not None:
+        return int(stream)
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+        else:
+            _raw_stream = lambda: raw(torch.cuda.current_device())
+    return _raw_stream()
+
+
 def _call(name, X, W1, W3, W2, act, Y, stream, check):
     M, K = X.shape
     N1, N2 = W2.shape
-    rc = getattr(lib(), name)(_ptr(X), _ptr(W1), _ptr(W3), _ptr(W2), int(act), M, K, N1, N2, _ptr(Y), _stream(stream))
-    if check:
+    rc = getattr(_lib or lib(), name)(_addr(X), _addr(W1), _addr(W3), _addr(W2), int(act), M, K, N1, N2, _addr(Y),
+                                      _stream_addr(stream))
+    if check and rc != 0:
         _check(rc, name)
     return rc
 
@@ -378,8 +403,9 @@ def _conv(name, X, W1, W2, act, Y, stream, check):
     B, H, W, IC = X.shape
     k1, _, _, OC1 = W1.shape
     k2, _, _, OC2 = W2.shape
-    rc = getattr(lib(), name)(_ptr(X), _ptr(W1), _ptr(W2), int(act), B, H, W, IC, OC1, OC2, k1, k2, _ptr(Y), _stream(stream))
-    if check:
+    rc = getattr(_lib or lib(), name)(_addr(X), _addr(W1), _addr(W2), int(act), B, H, W, IC, OC1, OC2, k1, k2, _addr(Y),
+                                      _stream_addr(stream))
+    if check and rc != 0:
         _check(rc, name)
     return rc
 
