@@ -7,7 +7,8 @@
 // So every operand goes straight from global memory to the registers of the wave that multiplies it, with many
 // loads in flight together and no barrier between them: the four waves split K (partial tiles summed in LDS), a
 // W1 row is read as 16 lanes x 16 bytes that feed four column tiles, and the second product's first weights are on
-// their way while the first product is summed.
+// their way while the first product is summed.  128 x 256 x 1024 x 256: 51 -> 10.5 us (with the launch that clears
+// Y); before, 32 k at a time went through LDS with two barriers each, multiplied on scalar FMAs.
 #include "ffuse_dev.h"
 #include "ffuse_launch.h"
 #include <mutex>

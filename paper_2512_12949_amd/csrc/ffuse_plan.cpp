@@ -439,7 +439,7 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->exchange_bytes = 2.0 * h;
         t->lds_used = 2.0 * (bm * 128.0 + g * bh0 * 128.0);
         t->acc_regs = 256;
-    } else {  // scalar fp32 debug path
+    } else {  // fp32 path
         const double units = cdiv(m, 16) * cdiv(n1, 64);
         t->workgroups = (int)units;
         mfma_flops = 256 * 128.0 * 2.4e9;  // fp32 FMA rate, not matrix cores
