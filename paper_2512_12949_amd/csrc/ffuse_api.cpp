@@ -176,7 +176,8 @@ std::array<int64_t, 6> table_key(int dtype, int gated, int64_t K, int64_t N1, in
 
 // a0: the plan for this call -- a tuned plan of M's bin if there is one that fits, else the
 // model's choice for exactly this M (computed once, then looked up).  ws_bytes: the workspace the
-// call will run in (0: none yet, nothing to fit).
+// call will run in (0: none; kUnknownWorkspace: none named yet, nothing to fit).
+constexpr size_t kUnknownWorkspace = SIZE_MAX;
 ffuse_plan_t lookup_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, size_t ws_bytes) {
     auto it = g.table.find(table_key(dtype, gated, K, N1, N2, ffuse::m_bin(M)));
     if (it != g.table.end() && ffuse::plan_valid(it->second.plan, dtype, gated, M, K, N1, N2) &&
@@ -990,7 +991,7 @@ int ffuse_plan_lookup(int dtype, int act, int gated, int64_t M, int64_t K, int64
     if (dtype < FFUSE_DT_BF16 || dtype > FFUSE_DT_F32) return FFUSE_ERR_ACT;
     if (M < 1 || K < 8 || N1 < 8 || N2 < 8) return FFUSE_ERR_SHAPE;
     std::lock_guard<std::mutex> lock(g.mu);
-    *out = lookup_plan(dtype, act, gated ? 1 : 0, M, K, N1, N2, g.reg.ptr ? g.reg.bytes : 0);
+    *out = lookup_plan(dtype, act, gated ? 1 : 0, M, K, N1, N2, g.reg.ptr ? g.reg.bytes : kUnknownWorkspace);
     if (tuned_ms) {
         auto it = g.table.find(table_key(dtype, gated ? 1 : 0, K, N1, N2, ffuse::m_bin(M)));
         *tuned_ms = (it != g.table.end() && std::memcmp(&it->second.plan, out, sizeof(*out)) == 0) ? it->second.ms : 0.0;

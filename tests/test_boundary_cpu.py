@@ -76,6 +76,20 @@ def test_plan_lookup_without_tuning_is_the_models_choice():
     ff.ffuse_plan_table_clear()
 
 
+def test_plan_lookup_without_a_workspace_has_nothing_to_fit():
+    """No workspace is registered here: the lookup answers with the model's choice whatever its size, also for the
+    small problems whose choice keeps planes of partial sums (128 x 384 x 1536 x 384), and with a plan entered by hand."""
+    ff.ffuse_plan_table_clear()
+    for shape, gated in [((128, 384, 1536, 384), False), ((128, 512, 256, 64), False), ((100, 264, 520, 264), True), ((700, 264, 2056, 520), False)]:
+        want = ff.ffuse_choose_plan(ff.DT_BF16, 2, gated, *shape).as_dict()
+        assert ff.ffuse_plan_lookup(ff.DT_BF16, 2, gated, *shape)[0].as_dict() == want, shape
+        assert ff.ffuse_plan_lookup(ff.DT_BF16, 2, gated, *shape)[0].as_dict() == want, shape
+    by_hand = ff.make_plan(ff.FAMILY_REDUCE, bm=32, bh=64, bk=32, splits=3)
+    ff.ffuse_plan_table_set(ff.DT_BF16, False, 128, 384, 1536, 384, by_hand, ms=0.02)
+    assert ff.ffuse_plan_lookup(ff.DT_BF16, 2, False, 100, 384, 1536, 384)[0].as_dict() == by_hand.as_dict()
+    ff.ffuse_plan_table_clear()
+
+
 def test_tune_validates_before_touching_the_device():
     import ctypes
     L = ff.lib()
