@@ -61,13 +61,14 @@ struct State {
     int rows_wgs = 0;
     int exch_wgs = 0;
     // plan table (Sec. 4.3: plans are fixed ahead of time per range of the dynamic dimension M
-    // and looked up at run time).  Key: dtype, gated, K, N1, N2 and either the M bin (plans
-    // measured by ffuse_tune) or, negated, the exact M (plans chosen by the model).
+    // and looked up at run time).  Key: dtype, gated, K, N1, N2, either the M bin (plans measured by
+    // ffuse_tune) or, negated, the exact M (plans chosen by the model), and the bytes of workspace a
+    // modelled plan was chosen for (-1: any).
     struct TableEntry {
         ffuse_plan_t plan;
         double ms;        // measured time of a tuned plan; 0 for a modelled one
     };
-    std::map<std::array<int64_t, 6>, TableEntry> table;
+    std::map<std::array<int64_t, 7>, TableEntry> table;
 };
 State g;
 
@@ -170,22 +171,22 @@ struct Timer {  // brackets the dominant kernel with events when profiling is on
     }
 };
 
-std::array<int64_t, 6> table_key(int dtype, int gated, int64_t K, int64_t N1, int64_t N2, int64_t m_or_bin) {
-    return {dtype, gated, K, N1, N2, m_or_bin};
+std::array<int64_t, 7> table_key(int dtype, int gated, int64_t K, int64_t N1, int64_t N2, int64_t m_or_bin, int64_t ws_bytes = -1) {
+    return {dtype, gated, K, N1, N2, m_or_bin, ws_bytes};
 }
 
 // a0: the plan for this call -- a tuned plan of M's bin if there is one that fits, else the
-// model's choice for exactly this M (computed once, then looked up).  ws_bytes: the workspace the
-// call will run in (0: none; kUnknownWorkspace: none named yet, nothing to fit).
-constexpr size_t kUnknownWorkspace = SIZE_MAX;
+// model's choice for exactly this M, else its choice among the plans that fit (each computed once,
+// then looked up).  ws_bytes: the workspace the call will run in (0: none; kAnyWorkspace: none named
+// yet, nothing to fit).  Where no plan fits, one that does not: the call is then refused.
 ffuse_plan_t lookup_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, size_t ws_bytes) {
+    const auto fits = [&](const ffuse_plan_t& p) { return ffuse::plan_workspace_bytes(p, dtype, gated, M, K, N1, N2) <= ws_bytes; };
     auto it = g.table.find(table_key(dtype, gated, K, N1, N2, ffuse::m_bin(M)));
-    if (it != g.table.end() && ffuse::plan_valid(it->second.plan, dtype, gated, M, K, N1, N2) &&
-        (!ws_bytes || ffuse::plan_workspace_bytes(it->second.plan, dtype, gated, M, K, N1, N2) <= ws_bytes))
+    if (it != g.table.end() && ffuse::plan_valid(it->second.plan, dtype, gated, M, K, N1, N2) && fits(it->second.plan))
         return it->second.plan;
+    ffuse_plan_t plan;
     const auto key = table_key(dtype + 64 * g.objective, gated, K, N1, N2, -M);   // (modelled plans: one slot per objective)
     it = g.table.find(key);
-    ffuse_plan_t plan;
     if (it != g.table.end()) {
         plan = it->second.plan;
     } else {
@@ -193,14 +194,14 @@ ffuse_plan_t lookup_plan(int dtype, int act, int gated, int64_t M, int64_t K, in
         if (g.table.size() > 4096) g.table.clear();
         g.table[key] = {plan, 0.0};
     }
-    if (!ffuse::is_direct(plan) || ffuse::plan_workspace_bytes(plan, dtype, gated, M, K, N1, N2) <= ws_bytes) return plan;
-    // the planes of the small row blocks want more than this workspace holds: the best of the other plans
-    const auto other = table_key(dtype + 256 + 64 * g.objective, gated, K, N1, N2, -M);
-    it = g.table.find(other);
+    if (fits(plan)) return plan;
+    const auto limited = table_key(dtype + 64 * g.objective, gated, K, N1, N2, -M, (int64_t)ws_bytes);
+    it = g.table.find(limited);
     if (it != g.table.end()) return it->second.plan;
-    ffuse::choose_plan(dtype, act, gated, M, K, N1, N2, &plan, g.objective, false);
+    ffuse_plan_t small;
+    if (ffuse::choose_plan(dtype, act, gated, M, K, N1, N2, &small, g.objective, ws_bytes)) plan = small;
     if (g.table.size() > 4096) g.table.clear();
-    g.table[other] = {plan, 0.0};
+    g.table[limited] = {plan, 0.0};
     return plan;
 }
 
@@ -991,7 +992,7 @@ int ffuse_plan_lookup(int dtype, int act, int gated, int64_t M, int64_t K, int64
     if (dtype < FFUSE_DT_BF16 || dtype > FFUSE_DT_F32) return FFUSE_ERR_ACT;
     if (M < 1 || K < 8 || N1 < 8 || N2 < 8) return FFUSE_ERR_SHAPE;
     std::lock_guard<std::mutex> lock(g.mu);
-    *out = lookup_plan(dtype, act, gated ? 1 : 0, M, K, N1, N2, g.reg.ptr ? g.reg.bytes : kUnknownWorkspace);
+    *out = lookup_plan(dtype, act, gated ? 1 : 0, M, K, N1, N2, g.reg.ptr ? g.reg.bytes : ffuse::kAnyWorkspace);
     if (tuned_ms) {
         auto it = g.table.find(table_key(dtype, gated ? 1 : 0, K, N1, N2, ffuse::m_bin(M)));
         *tuned_ms = (it != g.table.end() && std::memcmp(&it->second.plan, out, sizeof(*out)) == 0) ? it->second.ms : 0.0;

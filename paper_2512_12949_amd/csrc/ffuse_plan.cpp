@@ -123,7 +123,7 @@ bool direct_geometry(const ffuse_plan_t& p, int64_t M, int64_t N1, int64_t N2, D
     if (want > 32) return false;
     g->slices = (ns + want - 1) / want;
     g->ranges = (ns + g->slices - 1) / g->slices;
-    // (at least what the family's larger tiles ask for, so that no call is accepted or refused differently)
+    // (one range stores no plane, but asks for what the family's larger tiles ask for all the same)
     g->ws_bytes = ((size_t)4 * M * N2 * g->ranges + 255) & ~(size_t)255;
     return true;
 }
@@ -561,7 +561,7 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
 // Enumerates the plans the kernels implement, discards infeasible ones and ranks the rest by
 // predicted time (Sec. 4.3, Algorithm 2 up to the top-k list; the on-device profiling of that
 // list is ffuse_tune in the API layer).
-void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out, bool direct) {
+void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out) {
     (void)act;
     out->clear();
     ffuse_plan_t best;
@@ -573,7 +573,7 @@ void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1,
         out->push_back({0.0, best});
         return;
     }
-    for (int bm = 16; direct && bm <= 32; bm += 16) {
+    for (int bm = 16; bm <= 32; bm += 16) {
         const int ns = (int)((N1 + 63) / 64), most = std::min(ns, two_phase_max_splits(M, N2));
         for (int sp = 1;; sp = std::min(2 * sp, most)) {
             ffuse_plan_t p;
@@ -677,12 +677,17 @@ void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1,
     std::stable_sort(out->begin(), out->end(), [](const RankedPlan& x, const RankedPlan& y) { return x.t_pred < y.t_pred; });
 }
 
-void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, ffuse_plan_t* out, int objective, bool direct) {
+bool choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, ffuse_plan_t* out, int objective, size_t ws_limit) {
     std::vector<RankedPlan> r;
-    rank_plans(dtype, act, gated, M, K, N1, N2, &r, direct);
+    rank_plans(dtype, act, gated, M, K, N1, N2, &r);
+    // a limit takes out what does not fit, and the exchange family: its result depends on an even spread of the
+    // launch over the XCDs, which is no matter for a plan that nobody asked for
+    if (ws_limit != kAnyWorkspace)
+        r.erase(std::remove_if(r.begin(), r.end(), [&](const RankedPlan& c) {
+            return c.plan.family == FFUSE_FAMILY_EXCHANGE || plan_workspace_bytes(c.plan, dtype, gated, M, K, N1, N2) > ws_limit; }), r.end());
     if (r.empty()) {
         std::memset(out, 0, sizeof(*out));
-        return;
+        return false;
     }
     *out = r.front().plan;
     if (objective != FFUSE_OBJECTIVE_BYTES) {
@@ -696,7 +701,7 @@ void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1
             traffic_model(c.plan, dtype, gated, M, K, N1, N2, &t);
             if (t.feasible && t.fabric_bytes <= 0.5 * tb.fabric_bytes) { *out = c.plan; tb = t; }
         }
-        return;
+        return true;
     }
     // fewest bytes between the L2s and the rest of the memory system among the plans predicted within
     // kBytesObjectiveSlack of the fastest (the ranking is sorted: stop at the first plan beyond the slack)
@@ -709,6 +714,7 @@ void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1
         if (!t.feasible) continue;
         if (!have || t.fabric_bytes < best_bytes) { best_bytes = t.fabric_bytes; *out = c.plan; have = true; }
     }
+    return true;
 }
 
 size_t plan_workspace_bytes(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2) {

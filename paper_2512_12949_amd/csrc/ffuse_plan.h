@@ -89,13 +89,15 @@ struct RankedPlan {
     double t_pred;
     ffuse_plan_t plan;
 };
-void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out, bool direct = true);   // direct: the 16- and 32-row reduce plans too
+void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, std::vector<RankedPlan>* out);
 // objective: FFUSE_OBJECTIVE_TIME -- the plan with the smallest predicted time; FFUSE_OBJECTIVE_BYTES -- among the
 // plans predicted within kBytesObjectiveSlack of that time, the one that moves the fewest bytes between the L2s
 // and the rest of the memory system
 constexpr double kBytesObjectiveSlack = 1.35;
-void choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, ffuse_plan_t* out,
-                 int objective = FFUSE_OBJECTIVE_TIME, bool direct = true);
+// ws_limit: bytes of workspace there are; the choice is made among the plans that fit (false, and *out zero: none does)
+constexpr size_t kAnyWorkspace = SIZE_MAX;
+bool choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2, ffuse_plan_t* out,
+                 int objective = FFUSE_OBJECTIVE_TIME, size_t ws_limit = kAnyWorkspace);
 // Bytes of workspace a plan needs for this problem.
 size_t plan_workspace_bytes(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2);
 // The paper's bookkeeping of the search space (host arithmetic only; the chooser above enumerates the few
