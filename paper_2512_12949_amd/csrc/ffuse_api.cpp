@@ -424,14 +424,19 @@ int run_unfused_locked(int dtype, const void* X, const void* W1, const void* W3,
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (dtype != FFUSE_DT_F32) {
         const int gated = W3 != nullptr;
-        const auto key = table_key(dtype + 16, gated, K, N1, N2, -M);   // its own slot beside the fused plans
+        const size_t ws_bytes = w.ptr ? w.bytes : 0;
+        const auto key = table_key(dtype + 16, gated, K, N1, N2, -M, (int64_t)ws_bytes);   // its own slot beside the fused plans
         auto it = g.table.find(key);
         if (it == g.table.end()) {
             std::vector<ffuse::RankedPlan> ranked;
             ffuse::rank_plans(dtype, act, gated, M, K, N1, N2, &ranked);
-            ffuse_plan_t best{};
-            for (const auto& r : ranked)
-                if (r.plan.family == FFUSE_FAMILY_TWOPHASE) { best = r.plan; break; }
+            ffuse_plan_t best{};   // the first that fits the workspace (none: the first of all, and the call is refused)
+            for (const auto& r : ranked) {
+                if (r.plan.family != FFUSE_FAMILY_TWOPHASE) continue;
+                const bool fits = ffuse::plan_workspace_bytes(r.plan, dtype, gated, M, K, N1, N2) <= ws_bytes;
+                if (fits || best.family != FFUSE_FAMILY_TWOPHASE) best = r.plan;
+                if (fits) break;
+            }
             if (best.family != FFUSE_FAMILY_TWOPHASE) return FFUSE_ERR_PLAN;
             if (g.table.size() > 4096) g.table.clear();
             g.table[key] = {best, 0.0};

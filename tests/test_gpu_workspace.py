@@ -66,3 +66,22 @@ def test_the_best_plan_that_fits_runs(M, K, N1, N2, gated):
     if gated:      # (without a gate the rows family needs no workspace at all)
         assert ff.ffuse_ffn_ws(ff.DT_BF16, dev["X"], dev["W1"], dev["W3"], dev["W2"], w.act, Y, ws[: (sizes[0] - 256) // 16 * 16], check=False) == -5
         assert ff.ffuse_ffn_ws(ff.DT_BF16, dev["X"], dev["W1"], dev["W3"], dev["W2"], w.act, Y, None, check=False) == -5
+
+
+@pytest.mark.parametrize("M,K,N1,N2,gated", [(64, 264, 1304, 520, True), (333, 1016, 2744, 1016, False), (700, 264, 2056, 520, False)])
+def test_the_two_launch_path_takes_the_best_plan_that_fits(M, K, N1, N2, gated):
+    w, ref, dev = _problem(M, K, N1, N2, gated, 1102)
+    ranked = [p for p, _ in ff.ffuse_rank_plans(ff.DT_BF16, w.act, gated, M, K, N1, N2, 1024) if p.family == ff.FAMILY_TWOPHASE]
+    sizes = sorted({plan_bytes(p, M, N1, N2) for p in ranked})
+    Y = torch.empty((M, N2), dtype=torch.bfloat16, device="cuda")
+    for nbytes in (sizes[-1], sizes[len(sizes) // 2], sizes[0]):
+        print(f"two launches {(M, K, N1, N2)} gated={gated} workspace {nbytes}", flush=True)
+        ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        Y.fill_(float("nan"))
+        ff.ffuse_ffn_unfused_ws(ff.DT_BF16, dev["X"], dev["W1"], dev["W3"], dev["W2"], w.act, Y, ws)
+        torch.cuda.synchronize()
+        gu.check(Y, ref, "bf16", what=f"two launches, workspace of {nbytes}")
+        # the same bits as the fused call in the plan that should have run
+        first = next(p for p in ranked if plan_bytes(p, M, N1, N2) <= nbytes)
+        assert torch.equal(Y, gu.run(w, dev, plan=first))
+    assert ff.ffuse_ffn_unfused_ws(ff.DT_BF16, dev["X"], dev["W1"], dev["W3"], dev["W2"], w.act, Y, ws[: sizes[0] - 256], check=False) == -5
