@@ -776,11 +776,11 @@ int run_conv_chain(int dtype, const void* X, const void* W1, const void* W2, int
         if (!ffuse::plan_valid(plan, dtype, 0, M, K, OC1, OC2)) return FFUSE_ERR_PLAN;
         found = true;
     } else {
-        // the model's best plan among those the 3x3 loader's kernels implement: ranked once per shape, then
-        // looked up (its own key space in the plan table: dtype + 32)
-        const auto key = table_key(dtype + 32, 0, K, OC1, OC2, -M);
+        // the model's best plan among those the 3x3 loader's kernels implement and the workspace holds: ranked once
+        // per shape and workspace size, then looked up (its own key space in the plan table: dtype + 32)
+        const auto key = table_key(dtype + 32, 0, K, OC1, OC2, -M, (int64_t)ws.bytes);
         auto it = g.table.find(key);
-        if (it != g.table.end() && ffuse::plan_workspace_bytes(it->second.plan, dtype, 0, M, K, OC1, OC2) <= ws.bytes) {
+        if (it != g.table.end()) {
             plan = it->second.plan;
             found = true;
         } else {

@@ -5,9 +5,10 @@ import torch
 
 from paper_2512_12949_amd import binding as ff
 from paper_2512_12949_amd import inputs
-from paper_2512_12949_amd.inputs import ACT_GELU_TANH, ACT_SILU
+from paper_2512_12949_amd.inputs import ACT_GELU_TANH, ACT_RELU, ACT_SILU
 
 import gpu_util as gu
+import oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +86,30 @@ def test_the_two_launch_path_takes_the_best_plan_that_fits(M, K, N1, N2, gated):
         first = next(p for p in ranked if plan_bytes(p, M, N1, N2) <= nbytes)
         assert torch.equal(Y, gu.run(w, dev, plan=first))
     assert ff.ffuse_ffn_unfused_ws(ff.DT_BF16, dev["X"], dev["W1"], dev["W3"], dev["W2"], w.act, Y, ws[: sizes[0] - 256], check=False) == -5
+
+
+def test_a_3x3_chain_forgets_a_small_workspace():
+    """A plan picked because a small workspace was registered does not stay when a larger one is."""
+    w = inputs.ConvWorkload("ws3", 1, 14, 14, 64, 256, 256, 3, 1, "bf16", ACT_RELU, 610)
+    host = inputs.make_conv(w)
+    ref = oracle.conv_chain(host["X"], host["W1"], host["W2"], ACT_RELU, bf16=True)
+    dev = {k: gu.to_device(v, "bf16") for k, v in host.items()}
+    M, K = 14 * 14, 9 * 64
+    gu.Workspace.buf = None
+    seen = {}
+    for step, nbytes in enumerate((4 * M * 256 + 4096, 64 << 20, 4 * M * 256 + 4096, 64 << 20)):
+        ws = torch.full((nbytes // 256 * 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        ff.ffuse_set_workspace(ws)
+        Y = torch.full((1, 14, 14, 256), float("nan"), dtype=torch.bfloat16, device="cuda")
+        ff.ffuse_conv_chain(dev["X"], dev["W1"], dev["W2"], ACT_RELU, Y)
+        ff.ffuse_sync_status()
+        gu.check(Y.reshape(M, 256), ref.reshape(M, 256), "bf16", what=f"step {step}, workspace of {nbytes}")
+        last = ff.ffuse_last_plan()
+        assert plan_bytes(last, M, 256, 256) <= ws.numel()
+        assert seen.setdefault(nbytes, last.as_dict()) == last.as_dict(), f"step {step}"
+    assert len({tuple(p.items()) for p in seen.values()}) == 2
+    # the plan of the large workspace is the ranking's first among the loader's plans
+    first = next(p for p, _ in ff.ffuse_rank_plans(ff.DT_BF16, ACT_RELU, False, M, K, 256, 256, 1024)
+                 if (p.family == ff.FAMILY_TWOPHASE and p.bm <= 128 and p.bk != 32) or (p.family == ff.FAMILY_REDUCE and p.bm <= 32))
+    assert seen[64 << 20] == first.as_dict()
+    ff.ffuse_set_workspace(None)
