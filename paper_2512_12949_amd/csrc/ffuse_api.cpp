@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <array>
 #include <cstring>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <vector>
@@ -175,6 +176,14 @@ std::array<int64_t, 7> table_key(int dtype, int gated, int64_t K, int64_t N1, in
     return {dtype, gated, K, N1, N2, m_or_bin, ws_bytes};
 }
 
+// keeps a modelled plan.  A table that has grown large drops the modelled plans, which can be chosen again, and
+// keeps the measured ones.
+void remember(const std::array<int64_t, 7>& key, const ffuse_plan_t& plan) {
+    if (g.table.size() > 4096)
+        for (auto it = g.table.begin(); it != g.table.end();) it = it->first[5] < 0 ? g.table.erase(it) : std::next(it);
+    g.table[key] = {plan, 0.0};
+}
+
 // a0: the plan for this call -- a tuned plan of M's bin if there is one that fits, else the
 // model's choice for exactly this M, else its choice among the plans that fit (each computed once,
 // then looked up).  ws_bytes: the workspace the call will run in (0: none; kAnyWorkspace: none named
@@ -191,8 +200,7 @@ ffuse_plan_t lookup_plan(int dtype, int act, int gated, int64_t M, int64_t K, in
         plan = it->second.plan;
     } else {
         ffuse::choose_plan(dtype, act, gated, M, K, N1, N2, &plan, g.objective);
-        if (g.table.size() > 4096) g.table.clear();
-        g.table[key] = {plan, 0.0};
+        remember(key, plan);
     }
     if (fits(plan)) return plan;
     const auto limited = table_key(dtype + 64 * g.objective, gated, K, N1, N2, -M, (int64_t)ws_bytes);
@@ -200,8 +208,7 @@ ffuse_plan_t lookup_plan(int dtype, int act, int gated, int64_t M, int64_t K, in
     if (it != g.table.end()) return it->second.plan;
     ffuse_plan_t small;
     if (ffuse::choose_plan(dtype, act, gated, M, K, N1, N2, &small, g.objective, ws_bytes)) plan = small;
-    if (g.table.size() > 4096) g.table.clear();
-    g.table[limited] = {plan, 0.0};
+    remember(limited, plan);
     return plan;
 }
 
@@ -438,8 +445,7 @@ int run_unfused_locked(int dtype, const void* X, const void* W1, const void* W3,
                 if (fits) break;
             }
             if (best.family != FFUSE_FAMILY_TWOPHASE) return FFUSE_ERR_PLAN;
-            if (g.table.size() > 4096) g.table.clear();
-            g.table[key] = {best, 0.0};
+            remember(key, best);
             it = g.table.find(key);
         }
         const ffuse_plan_t keep = g.last_plan;
@@ -578,8 +584,8 @@ int ffuse_ffn_static(int dtype, const void* X, const void* W1, const void* W3, c
         for (const auto& r : ranked)
             if (ffuse::plan_workspace_bytes(r.plan, dtype, gated, M, K, N1, N2) <= kStaticScratchBytes) { fit = &r; break; }
         if (!fit) return FFUSE_ERR_WORKSPACE;     // the problem is too large for the built-in scratch memory
-        if (g.table.size() > 4096) g.table.clear();
-        it = g.table.insert({key, {fit->plan, 0.0}}).first;
+        remember(key, fit->plan);
+        it = g.table.find(key);
     }
     g.no_alloc_call = true;
     rc = run_plan(it->second.plan, dtype, X, W1, W3, W2, act, M, K, N1, N2, Y, *w, stream);
@@ -793,10 +799,7 @@ int run_conv_chain(int dtype, const void* X, const void* W1, const void* W2, int
                     found = true;
                     break;
                 }
-            if (found) {
-                if (g.table.size() > 4096) g.table.clear();
-                g.table[key] = {plan, 0.0};
-            }
+            if (found) remember(key, plan);
         }
     }
     if (!found) return FFUSE_ERR_WORKSPACE;

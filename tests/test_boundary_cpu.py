@@ -90,6 +90,19 @@ def test_plan_lookup_without_a_workspace_has_nothing_to_fit():
     ff.ffuse_plan_table_clear()
 
 
+def test_many_modelled_shapes_do_not_push_out_a_measured_plan():
+    """The table drops modelled plans when it grows past its limit (4096 entries), never the measured ones."""
+    ff.ffuse_plan_table_clear()
+    plan = ff.make_plan(ff.FAMILY_TWOPHASE, bm=128, bh=64, bk=32, bn2=256, splits=4, h_level=2, raster=2)
+    ff.ffuse_plan_table_set(ff.DT_BF16, False, 200, 4096, 16384, 4096, plan, ms=0.125)
+    p, L = ff.Plan(), ff.lib()
+    for M in range(1, 4300):      # (fp32: one candidate per shape, quick to choose)
+        assert L.ffuse_plan_lookup(ff.DT_F32, 2, 0, M, 64, 64, 64, ctypes.byref(p), None) == 0
+    got, ms = ff.ffuse_plan_lookup(ff.DT_BF16, 2, False, 256, 4096, 16384, 4096)
+    assert got.as_dict() == plan.as_dict() and ms == 0.125
+    ff.ffuse_plan_table_clear()
+
+
 def test_tune_validates_before_touching_the_device():
     import ctypes
     L = ff.lib()
