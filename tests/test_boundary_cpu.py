@@ -180,6 +180,61 @@ def test_streamed_weights_get_one_row_block():
     assert p.family == ff.FAMILY_TWOPHASE and p.bm in (64, 128)
 
 
+def _item(MB, S, raster, grp, idx):
+    total = MB * S
+    per = -(-total // 8)
+    v = grp * per + idx
+    if idx >= per or v >= total:
+        return None
+    panel, rem = divmod(v, raster * S)
+    rows = min(raster, MB - panel * raster)
+    return panel * raster + rem % rows, rem // rows
+
+
+def _independent(M, N1, N2, bm, bh1, splits, raster):
+    MB, NS1, NCB = -(-M // bm), -(-N1 // bh1), -(-N2 // 256)
+    raster = min(raster, MB)
+    ksplit = -(-(-(-N1 // splits)) // 64) * 64
+    splits = -(-N1 // ksplit)
+    owner = {}
+    for g in range(8):
+        idx = 0
+        while (it := _item(MB, NS1, raster, g, idx)) is not None:
+            owner[it] = g
+            idx += 1
+    for g in range(8):
+        idx = 0
+        while (it := _item(MB, NCB * splits, raster, g, idx)) is not None:
+            rb, u = it
+            sp = u // NCB
+            k0, k1 = sp * ksplit, min(N1, (sp + 1) * ksplit)
+            s = k0 // bh1
+            while s * bh1 < k1:
+                if owner[(rb, s)] != g:
+                    return False
+                s += 1
+            idx += 1
+    return True
+
+
+def test_group_local_barrier_condition_of_256_column_slices_in_128_row_blocks():
+    """The same enumeration for the ungated 128 x 256 first-phase tiles; a gated chain's 128-row plan with bh = 256
+    keeps slices of 128."""
+    import random
+    rng = random.Random(8)
+    cases = [(512, 4096, 16384, 4096, False, 4, 4), (300, 200, 840, 264, False, 3, 4), (128, 264, 4096, 2048, False, 8, 1)]
+    for _ in range(60):
+        cases.append((rng.randint(1, 2000), 8 * rng.randint(8, 64), 8 * rng.randint(1, 1500), 8 * rng.randint(1, 300), rng.random() < 0.3,
+                      rng.choice([1, 2, 3, 4, 8, 16]), rng.choice([1, 2, 4, 8])))
+    seen = set()
+    for M, K, N1, N2, gated, splits, raster in cases:
+        plan = ff.make_plan(ff.FAMILY_TWOPHASE, bm=128, bh=256, bn2=256, bk=32, splits=splits, raster=raster)
+        got = ff.ffuse_plan_group_local(plan, ff.DT_BF16, gated, M, K, N1, N2)
+        assert got == _independent(M, N1, N2, 128, 128 if gated else 256, splits, raster), (M, K, N1, N2, gated, splits, raster)
+        seen.add(got)
+    assert seen == {True, False}
+
+
 def test_group_local_barrier_condition_matches_the_item_maps():
     """Host logic of the two-phase family's barrier scope: ffuse_plan_group_local must say 1
     exactly when every second-phase item of a workgroup group reads only tiles of the
@@ -188,41 +243,6 @@ def test_group_local_barrier_condition_matches_the_item_maps():
     consecutive items each; within a group's range, patches of `raster` row blocks x all slices,
     row block fastest)."""
     import random
-
-    def item(MB, S, raster, grp, idx):
-        total = MB * S
-        per = -(-total // 8)
-        v = grp * per + idx
-        if idx >= per or v >= total:
-            return None
-        panel, rem = divmod(v, raster * S)
-        rows = min(raster, MB - panel * raster)
-        return panel * raster + rem % rows, rem // rows
-
-    def independent(M, N1, N2, bm, bh1, splits, raster):
-        MB, NS1, NCB = -(-M // bm), -(-N1 // bh1), -(-N2 // 256)
-        raster = min(raster, MB)
-        ksplit = -(-(-(-N1 // splits)) // 64) * 64
-        splits = -(-N1 // ksplit)
-        owner = {}
-        for g in range(8):
-            idx = 0
-            while (it := item(MB, NS1, raster, g, idx)) is not None:
-                owner[it] = g
-                idx += 1
-        for g in range(8):
-            idx = 0
-            while (it := item(MB, NCB * splits, raster, g, idx)) is not None:
-                rb, u = it
-                sp = u // NCB
-                k0, k1 = sp * ksplit, min(N1, (sp + 1) * ksplit)
-                s = k0 // bh1
-                while s * bh1 < k1:
-                    if owner[(rb, s)] != g:
-                        return False
-                    s += 1
-                idx += 1
-        return True
 
     rng = random.Random(7)
     cases = [(4096, 4096, 16384, 4096, False, 256, 256, 1, 4), (4096, 4096, 16384, 4096, False, 256, 256, 1, 2),
@@ -243,7 +263,7 @@ def test_group_local_barrier_condition_matches_the_item_maps():
             got = ff.ffuse_plan_group_local(plan, ff.DT_BF16, gated, M, K, N1, N2)
         except ff.FfuseError:
             continue        # not a plan the kernels implement for this shape
-        want = independent(M, N1, N2, bm, bh1, splits, raster)
+        want = _independent(M, N1, N2, bm, bh1, splits, raster)
         assert got == want, (M, K, N1, N2, gated, bm, bh1, splits, raster, got, want)
         seen.add(got)
     assert seen == {True, False}

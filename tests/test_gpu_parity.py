@@ -234,8 +234,7 @@ def test_two_phase_narrow_hidden_slices(dtype, gated):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_two_phase_wide_slices_in_128_row_blocks(dtype):
     """128 x 256 first-phase tiles: one ragged tile, a ragged second slice and row block, more items than
-    workgroups; K shorter and longer than the ring; direct output and partial planes; the weight-load hint
-    is a template twin and rides along through the environment elsewhere."""
+    workgroups; K shorter and longer than the ring; direct output and partial planes."""
     for (M, K, N1, N2) in [(100, 40, 248, 264), (300, 200, 840, 264), (520, 328, 16904, 72)]:
         w, host, dev = _case("wide", M, K, N1, N2, dtype, ACT_GELU_TANH, False)
         rows = inputs.sample_rows(M, 128, 24, seed=3)
@@ -271,6 +270,36 @@ def test_two_phase_non_temporal_weight_streaming(dtype, gated, monkeypatch):
             gu.check(hinted, ref, dtype, what=f"non-temporal bm={bm} bh={bh} bk={bk}")
             assert torch.equal(plain, hinted)
     monkeypatch.delenv("FFUSE_NT")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_two_phase_wide_slices_with_non_temporal_weight_streaming(dtype, monkeypatch):
+    """The 128 x 256 first-phase tiles' twin that streams the weights with the non-temporal hint: the same bits."""
+    for (M, K, N1, N2) in [(100, 40, 248, 264), (128, 200, 840, 264), (300, 328, 1304, 136)]:
+        w, host, dev = _case("ntw", M, K, N1, N2, dtype, ACT_GELU_TANH, False)
+        ref = gu.oracle_rows(w, host)
+        for splits, raster in ((1, 2), (3, 2)):
+            plan = ff.make_plan(ff.FAMILY_TWOPHASE, bm=128, bh=256, bk=32, splits=splits, raster=raster)
+            print(f"non-temporal wide slices {dtype} shape {(M, K, N1, N2)} splits={splits}", flush=True)
+            monkeypatch.setenv("FFUSE_NT", "0")
+            plain = gu.run(w, dev, plan=plan)
+            monkeypatch.setenv("FFUSE_NT", "1")
+            hinted = gu.run(w, dev, plan=plan)
+            gu.check(hinted, ref, dtype, what=f"non-temporal wide slices splits={splits}")
+            assert torch.equal(plain, hinted)
+    monkeypatch.delenv("FFUSE_NT")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_split_gate_in_wide_slices(dtype):
+    """Branches on different workgroups in 128 x 256 single-branch tiles: the pass that joins them walks slices of 256."""
+    for (M, K, N1, N2) in [(100, 40, 320, 264), (300, 200, 832, 136), (520, 72, 1088, 72)]:
+        w, host, dev = _case("splitw", M, K, N1, N2, dtype, ACT_SILU, True)
+        ref = gu.oracle_rows(w, host)
+        for splits, raster in ((1, 2), (3, 1)):
+            plan = ff.make_plan(ff.FAMILY_TWOPHASE, bm=128, bh=256, bk=32, splits=splits, raster=raster, gate_split=1)
+            print(f"split gate, wide slices {dtype} shape {(M, K, N1, N2)} splits={splits}", flush=True)
+            gu.check(gu.run(w, dev, plan=plan), ref, dtype, what=f"split gate, wide slices splits={splits}")
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])

@@ -23,6 +23,8 @@ def _plans(gated, N1):
         "two-phase 256": ff.make_plan(ff.FAMILY_TWOPHASE, bm=256, splits=2, raster=4),
         "reduce": ff.make_plan(ff.FAMILY_REDUCE, 128, 64, bn2=128, raster=1, splits=(N1 + 63) // 64),
         "exchange": ff.make_plan(ff.FAMILY_EXCHANGE, 256, 128 if gated else 256, bn2=256, raster=1, splits=1, producers=16, ring=32),
+        "small rows direct": ff.make_plan(ff.FAMILY_REDUCE, bm=16, bh=64, bk=32, splits=1),
+        "small rows planes": ff.make_plan(ff.FAMILY_REDUCE, bm=16, bh=64, bk=32, splits=5),
     }
 
 
@@ -56,7 +58,8 @@ def test_inputs_that_change_from_call_to_call(gated):
             gu.check(Y, refs[i], "bf16", what=f"{name} call {rep} (input {i})")
 
 
-@pytest.mark.parametrize("kind", ["two-phase direct", "two-phase planes", "two-phase 256", "reduce", "exchange", "rows"])
+@pytest.mark.parametrize("kind", ["two-phase direct", "two-phase planes", "two-phase 256", "reduce", "exchange", "rows",
+                                  "small rows direct", "small rows planes"])
 def test_graph_replays_with_inputs_overwritten_in_place(kind):
     """A captured call is replayed after its input buffer was overwritten in place and after an eager
     call of ANOTHER family has used (and dirtied) the same workspace: every replay must give the
@@ -96,6 +99,58 @@ def test_graph_replays_with_inputs_overwritten_in_place(kind):
             gu.check(Y, refs[i], "bf16", what=f"{kind} replay {rep} (input {i})")
     finally:
         ff.ffuse_force_plan(None)
+
+
+@pytest.mark.parametrize("gated", [False, True])
+def test_small_row_planes_between_the_calls_of_other_families(gated):
+    """Planes of the small row blocks lie over what other families leave in a workspace for their next call: over the
+    reduce family's zeros always, over the two-phase family's clean barrier flags where they reach that far (6 planes
+    do, 2 do not).  Calls in turn on one workspace, eager and from a graph."""
+    act = ACT_SILU if gated else ACT_GELU_TANH
+    w = inputs.custom("smallp", 200, 136, 328, 264, dtype="bf16", act=act, gated=gated, cfg_id=985)
+    hosts = _variants(w, 3)
+    refs = [gu.oracle_rows(w, h) for h in hosts]
+    devs = [{k: gu.to_device(v, "bf16") for k, v in h.items()} for h in hosts]
+    two = ff.make_plan(ff.FAMILY_TWOPHASE, bm=128, bh=64, bk=32, splits=3, raster=1)
+    flags = 4 * w.M * w.N2 * 3 + 2 * w.M * w.N1                       # where the two-phase plan's flags lie
+    small = [ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=sp) for bm, sp in ((16, 6), (32, 2), (16, 3), (16, 1))]
+    assert 4 * w.M * w.N2 * 6 > flags > 4 * w.M * w.N2 * 3
+    reduce = ff.make_plan(ff.FAMILY_REDUCE, 128, 64, bn2=128, raster=1, splits=(w.N1 + 63) // 64)
+    gu.run(w, devs[0], plan=small[0])                                 # (sizes the workspace)
+    n = 0
+    for others in ((two,), (reduce,), (two, reduce)):
+        for s in small:
+            for _ in range(2):
+                for p in (s, *others):
+                    i, n = n % 3, n + 1
+                    gu.check(gu.run(w, devs[i], plan=p), refs[i], "bf16", what=f"call {n}: {p.as_dict()}")
+    X = devs[0]["X"].clone()
+    Y = torch.zeros((w.M, w.N2), dtype=torch.bfloat16, device="cuda")
+    side = torch.cuda.Stream()
+    for s in small[:2]:
+        ff.ffuse_force_plan(s)
+        try:
+            with torch.cuda.stream(side):
+                ff.ffuse_ffn(X, devs[0]["W1"], devs[0]["W3"], devs[0]["W2"], w.act, Y)
+                side.synchronize()
+                g = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(g, stream=side):
+                    ff.ffuse_ffn(X, devs[0]["W1"], devs[0]["W3"], devs[0]["W2"], w.act, Y)
+        finally:
+            ff.ffuse_force_plan(None)
+        torch.cuda.synchronize()
+        for rep in range(6):
+            i = (rep + 1) % 3
+            X.copy_(devs[i]["X"])
+            p = (two, reduce)[rep % 2]
+            gu.check(gu.run(w, devs[i], plan=p), refs[i], "bf16", what=f"between replays: {p.as_dict()}")
+            Y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            gu.check(Y, refs[i], "bf16", what=f"replay {rep} of {s.as_dict()}")
+    gu.Workspace.buf = None
+    ff.ffuse_set_workspace(None)
 
 
 def test_a_barrier_wait_that_expires_is_reported_and_does_not_poison_the_next_call():
@@ -239,3 +294,27 @@ def test_seeded_walk_over_every_family():
         what = f"walk {n}: {fam} {(M, K, N1, N2)} gated={gated} {dtype} act={act}"
         print(what, flush=True)
         gu.check(gu.run(w, dev, plan=plan), gu.oracle_rows(w, host), dtype, what=what)
+
+
+def test_seeded_walk_over_small_row_blocks_and_wide_slices():
+    """The walk above for the 16- and 32-row reduce tiles and the 128 x 256 first-phase tiles, on the same workspace."""
+    import random
+    rng = random.Random(20260102)
+    for n in range(32):
+        fam = rng.choice(["small", "small", "wide"])
+        gated = rng.random() < 0.5 and fam == "small"
+        dtype, act = rng.choice(["bf16", "f16"]), rng.choice([0, 1, 2, 3])
+        M = rng.choice([1, 15, 33, 64, 130, 257, 520])
+        K, N1, N2 = 8 * rng.randint(1, 150), 8 * rng.randint(1, 200), 8 * rng.randint(1, 160)
+        if fam == "small":
+            bm = rng.choice([16, 32]) if N2 <= 512 else 16
+            plan = ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=rng.choice([1, 2, 5, 32]))
+        else:
+            plan = ff.make_plan(ff.FAMILY_TWOPHASE, bm=128, bh=256, bk=32, splits=rng.choice([1, 2, 5]), raster=rng.choice([1, 2, 4]))
+        w = inputs.custom("walk2", M, K, N1, N2, dtype=dtype, act=act, gated=gated, cfg_id=1200 + n)
+        host = inputs.make(w)
+        dev = {k: gu.to_device(v, dtype) for k, v in host.items()}
+        what = f"walk {n}: {fam} {(M, K, N1, N2)} gated={gated} {dtype} act={act} {plan.as_dict()}"
+        print(what, flush=True)
+        gu.check(gu.run(w, dev, plan=plan), gu.oracle_rows(w, host), dtype, what=what)
+        assert ff.ffuse_sync_status(check=False) == 0
