@@ -429,7 +429,7 @@ __global__ __launch_bounds__(256) void fused_two_phase_kernel(TwoPhaseArgs a) {
 // The loads of BATCH planes are issued together and only then summed: the pass is latency-bound on small
 // outputs (the planes were written by other XCDs and come from behind the L2), and one round trip per plane
 // instead of one per eight made every call on the small shapes 1.2-1.5 us longer.  For the same reason small outputs
-// go out four to a thread (V = 1) in blocks of one wave, sixteen planes at a time: more of the chip's load paths wait
+// of many planes go out four to a thread (V = 1) in blocks of one wave, sixteen planes at a time: more of the chip's load paths wait
 // side by side (a whole call of 128 x 384 x 1536 x 384 11.9 -> 10.8 us, 1 x 4096 x 11008 x 4096 gated 73.0 -> 71.7).
 template <typename T, int BATCH, int V> __global__ __launch_bounds__(256) void finalize_planes_kernel(const float* __restrict__ part, void* __restrict__ Y,
                                                                                         int64_t units, int64_t plane_elems, int planes) {
@@ -466,9 +466,10 @@ template <typename T, int BATCH, int V> __global__ __launch_bounds__(256) void f
 }
 
 template <typename T> static void finalize_planes(const float* part, void* Y, int64_t count, int planes, hipStream_t st) {
-    // Up to 128 K outputs.  (49 K, 24 planes: 1.1 us faster than eight outputs to a thread in blocks of four waves;
-    // 200 K outputs, 4 planes: 0.4 us slower, and larger ones, bound by bandwidth, no faster.)
-    if (count <= 131072) {
+    // Up to 128 K outputs of more than four planes.  Whole calls of 33-131 K outputs, eight outputs to a thread in blocks of
+    // four waves -> this: 2 planes even, 4 planes 0.1-0.3 us slower, 6 planes 0.05-0.15 faster, 8 planes 0.1-0.3, 12 planes
+    // 0-0.9, 16-32 planes 0.6-2.5.  (164 K and more outputs, bound by bandwidth: even at every count of planes.)
+    if (count <= 131072 && planes > 4) {
         const int64_t n4 = count / 4;
         hipLaunchKernelGGL((finalize_planes_kernel<T, 16, 1>), dim3((unsigned)((n4 + 63) / 64)), dim3(64), 0, st, part, Y, n4, count, planes);
     } else {
