@@ -29,7 +29,8 @@
  *     ((M + 256) N1 elements of the operand type: rows are independent, a taller problem is two
  *     calls).  Anything else returns FFUSE_ERR_SHAPE.
  *   - Errors are returned as negative status codes; nothing is written on a validation error.
- *   - The fused and unfused paths need a caller-owned workspace of ffuse_workspace_bytes: either
+ *   - The fused and unfused paths need a caller-owned workspace of ffuse_workspace_bytes (a smaller one
+ *     runs the best plan that fits, FFUSE_ERR_WORKSPACE where none does): either
  *     ONE registered with ffuse_set_workspace and used by every call that does not name another,
  *     or one passed per call (ffuse_ffn_ws, ffuse_ffn_unfused_ws).  A call leaves its workspace
  *     ready for the next call on the same stream.  Calls that overlap in time (different
@@ -154,7 +155,7 @@ typedef struct {
 } ffuse_traffic_t;
 
 /* ---- the fused chain.  bf16 operands and output; _f16 / _f32 twins take the same
- *      arguments (fp32 is a debug mode on plain FMA).  Returns a ffuse_status_t. ---------- */
+ *      arguments (fp32: a debug mode in full fp32 products and sums).  Returns a ffuse_status_t. */
 int ffuse_ffn(const void* X, const void* W1, const void* W3 /* NULL = not gated */, const void* W2,
               int act, int64_t M, int64_t K, int64_t N1, int64_t N2, void* Y, void* stream);
 int ffuse_ffn_f16(const void* X, const void* W1, const void* W3, const void* W2, int act, int64_t M,
@@ -210,8 +211,8 @@ int ffuse_ffn_unfused_f32(const void* X, const void* W1, const void* W3, const v
  *      X[B][H][W][IC] and Y[B][H][W][OC2] channels-last, W1[k1][k1][IC][OC1],
  *      W2[k2][k2][OC1][OC2]; bf16 (or fp16 for the _f16 twin), device pointers as above.
  *      Built: k2 = 1 with k1 = 1 (the standard chain on the B*H*W pixel rows, any plan) or
- *      k1 = 3 (two-phase kernel whose first product gathers the 3x3 neighbourhood while
- *      loading; needs IC % 64 == 0).  Other kernel sizes return FFUSE_ERR_SHAPE.  IC, OC1, OC2
+ *      k1 = 3 (two-phase kernel or small-row-block reduce kernel, whose first product gathers the
+ *      3x3 neighbourhood while loading; needs IC % 64 == 0).  Other kernel sizes return FFUSE_ERR_SHAPE.  IC, OC1, OC2
  *      multiples of 8.  Workspace: ffuse_workspace_bytes(dtype, 0, B*H*W, k1*k1*IC, OC1, OC2, 0). */
 int ffuse_conv_chain(const void* X, const void* W1, const void* W2, int act, int64_t B, int64_t H,
                      int64_t W, int64_t IC, int64_t OC1, int64_t OC2, int k1, int k2, void* Y, void* stream);

@@ -8,7 +8,9 @@
 // loads in flight together and no barrier between them: the four waves split K (partial tiles summed in LDS), a
 // W1 row is read as 16 lanes x 16 bytes that feed four column tiles, and the second product's first weights are on
 // their way while the first product is summed.  128 x 256 x 1024 x 256: 51 -> 10.5 us (with the launch that clears
-// Y); before, 32 k at a time went through LDS with two barriers each, multiplied on scalar FMAs.
+// Y); before, 32 k at a time went through LDS with two barriers each, multiplied on scalar FMAs.  Many rows: 2048 x 512 x
+// 2048 x 512 761 -> 152 us, 2048 x 1024 x 4096 x 1024 2825 -> 485 (71 TFLOP/s), gated 3756 -> 606 (85), 8192 x 256 x 1024 x
+// 256 774 -> 153; there every row block reads the weights again and an output takes N1 / 64 atomic adds.
 #include "ffuse_dev.h"
 #include "ffuse_launch.h"
 #include <mutex>
@@ -52,8 +54,8 @@ __device__ __forceinline__ void load_rows_f32(__amdgpu_buffer_rsrc_t r, int k, u
 
 // H block [16][64] of act(X W1) [.* X W3] for rows m0.., hidden n0.. into hs (LDS).  part: a partial tile a wave
 // (and branch).  Ends with a barrier.  The groups of 16 k are dealt to the waves in turn, BATCH at a time each:
-// 64 registers of operands in flight (K <= 256: all of a wave's loads are issued at once).  Rows past M, k past K
-// and columns past N1 read as zeros (K, N1 and N2 are multiples of 8).
+// 80 registers of operands in flight, gated 72 (up to K = 256, gated 128, all of a wave's loads are issued at once).
+// Rows past M, k past K and columns past N1 read as zeros (K, N1 and N2 are multiples of 8).
 template <bool GATED>
 static __device__ __forceinline__ void first_product_f32(const float* X, const float* W1, const float* W3,
                                                          int64_t M, int K, int N1, int act, int64_t m0, int n0,
