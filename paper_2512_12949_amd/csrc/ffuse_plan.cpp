@@ -47,7 +47,8 @@ void set_device_units(int cus) {
 }
 
 static double cdiv(double a, double b) { return std::ceil(a / b); }
-static constexpr double kRowsEff = 0.45;   // rows family: fraction of the MFMA peak its chunk loop sustains at K = N2 = 1024 (bound by the L2 -> LDS load path)
+static constexpr double kRowsEff = 0.45;   // rows family: fraction of the MFMA peak its chunk loop sustains at K = N2 = 1024 (bound by the L2 -> LDS load path) ...
+static constexpr double kRowsEffSmall = 0.38;   // ... and at K = N2 = 512
 static constexpr double kRowsLdsModel = 4 * 4 * 4096 + 12 * 4096 + 64 * 128;   // rows family: rings, partial tiles, H chunk
 
 bool plan_valid(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64_t K, int64_t N1, int64_t N2) {
@@ -244,10 +245,10 @@ bool fused_reduce_tile_ok(int gated, int bm, int bh) {
 // more of the loop is LDS reads rather than matrix instructions.  The 256 x 256 tile runs at
 // the chip's power limit; smaller tiles run at a higher clock but stay LDS-bound.
 //     wave tile    r     LDS-direct loop   register-staged loop
-//     128 x 128    1     0.51              --
-//      64 x 128    1.5   0.46              0.40
-//      64 x 64     2     0.36              0.275
-//      64 x 32     3     0.27              0.156
+//     128 x 128    1     0.498             --
+//      64 x 128    1.5   0.455             0.40
+//      64 x 64     2     0.348             0.275
+//      64 x 32     3     0.277             0.156
 // (LDS-direct below 256 rows: the loop that loads the row operand in whole cache lines; with
 // half lines it measured 0.40 / 0.31 / 0.20)
 // 1 / efficiency is interpolated linearly in r (and extrapolated beyond 3).
@@ -255,8 +256,8 @@ static double block_gemm_efficiency(double rows, double cols, bool lds_direct) {
     const double wr = rows >= 128.0 ? rows / 2.0 : rows, wc = rows >= 128.0 ? cols / 2.0 : cols / 4.0;
     const double r = 64.0 * (1.0 / wr + 1.0 / wc);
     static const double rs[4] = {1.0, 1.5, 2.0, 3.0};
-    static const double inv_direct[4] = {1.0 / 0.51, 1.0 / 0.46, 1.0 / 0.36, 1.0 / 0.27};
-    static const double inv_staged[4] = {1.0 / 0.51, 1.0 / 0.40, 1.0 / 0.275, 1.0 / 0.156};
+    static const double inv_direct[4] = {1.0 / 0.498, 1.0 / 0.455, 1.0 / 0.348, 1.0 / 0.277};
+    static const double inv_staged[4] = {1.0 / 0.498, 1.0 / 0.40, 1.0 / 0.275, 1.0 / 0.156};
     const double* inv = lds_direct ? inv_direct : inv_staged;
     if (r <= rs[0]) return 1.0 / inv[0];
     int i = 0;
@@ -299,20 +300,21 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
     t->feasible = 1;
 
     if (is_direct(p)) {
-        // Fitted on 33 shapes (1-32768 rows, K 8-4608, N2 8-2048), within about 15 % where the family is worth
-        // running.  A slice of 64 hidden columns costs two barriers and the issue of its loads: up to K = 256
-        // 0.9 us + 4 ns per k; beyond, 1.27 us per turn of the operand ring (512 k, gated 256) and 0.54 per block of
-        // 256 output columns.  32 rows take 1.33 times as long as 16.  Workgroups run one per CU; two of the smallest
-        // variant share one and then take 0.72 of twice the time.  Planes: their bytes, a second launch, eight at a time.
+        // Fitted with the two-phase constants below (see there): the measured calls of plans worth running scatter by 8 %
+        // round it.  A slice of 64 hidden columns costs two barriers and the issue of its loads: up to K = 256
+        // 1.05 us + 3.7 ns per k (gated 1.3 of that); beyond, 1.43 us per turn of the operand ring (512 k, gated 256: 1.55)
+        // and 0.56 per block of 256 output columns.  32 rows take 1.42 times as long as 16.  Workgroups run one per CU;
+        // two of the smallest variant share one and then take 0.9 of twice the time.  Planes: their bytes, a second
+        // launch, eight at a time.
         DirectGeometry dg;
         t->feasible = direct_geometry(p, M, N1, N2, &dg) ? 1 : 0;
         if (!t->feasible) return;
-        const double mb = cdiv(m, dg.bm), wgs = mb * dg.ranges, big = dg.bm == 32 ? 1.33 : 1.0;
+        const double mb = cdiv(m, dg.bm), wgs = mb * dg.ranges, big = dg.bm == 32 ? 1.42 : 1.0;
         const bool shortk = K <= 256 && dg.ng <= 2;
-        const double slice = 1e-6 * big * (shortk ? (0.9 + 0.004 * k) * (gated ? 1.3 : 1.0)
-                                                  : 0.5 + (gated ? 1.15 * cdiv(k, 256.0) : 1.27 * cdiv(k, 512.0)) + 0.54 * dg.ng);
+        const double slice = 1e-6 * big * (shortk ? (1.05 + 0.00368 * k) * (gated ? 1.3 : 1.0)
+                                                  : 0.198 + (gated ? 1.55 * cdiv(k, 256.0) : 1.43 * cdiv(k, 512.0)) + 0.556 * dg.ng);
         double rounds = cdiv(wgs, d.cus);
-        if (shortk && dg.ng == 1 && rounds > 1.0) rounds *= 0.72;
+        if (shortk && dg.ng == 1 && rounds > 1.0) rounds *= 0.9;
         const double weights = e * (g * k * n1 + n1 * n2), planes = dg.ranges > 1 ? 2.0 * 4.0 * m * n2 * dg.ranges : 0.0;
         t->workgroups = (int)std::min(wgs, (double)d.cus);
         t->l2_bytes = mb * weights + e * m * k * dg.ranges;
@@ -325,12 +327,8 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->t_fabric = t->fabric_bytes / d.fabric_bw;
         t->t_l2 = t->l2_bytes / d.l2_bw;
         t->t_mfma = rounds * dg.slices * slice;
-        t->t_reduce = dg.ranges > 1 ? planes / (0.5 * d.fabric_bw) + 2e-6 + 0.6e-6 * cdiv(dg.ranges, 8.0) : 0.0;
-        t->t_pred = 2.9e-6 + std::max({t->t_mfma, t->t_hbm, t->t_fabric}) + t->t_reduce;
-        // The two-phase prediction errs on the safe side where the two meet (measured 0.75-0.9 of it, gated 0.68-0.86:
-        // 200 x 1024 x 4096 x 1024 34 predicted and 28 measured, against 33 and 34 here; gated 16 x 1024 x 4096 x 1024
-        // 32 and 22, against 23 and 24), so this one is ranked with the same margin.
-        t->t_pred *= gated ? 1.45 : 1.2;
+        t->t_reduce = dg.ranges > 1 ? planes / (0.492 * d.fabric_bw) + 1.56e-6 + 0.421e-6 * cdiv(dg.ranges, 8.0) : 0.0;
+        t->t_pred = 2.49e-6 + std::max({t->t_mfma, t->t_hbm, t->t_fabric}) + t->t_reduce;
         return;
     }
     if (p.family == FFUSE_FAMILY_REDUCE) {
@@ -466,14 +464,15 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
     worst = std::max(worst, t->t_reduce) + (1.0 - overlap) * std::min(worst, t->t_reduce);
     const double launches = 2.0;  // main kernel + finalise / second GEMM / zero fill
     t->t_pred = worst + launches * d.launch_s;
-    // the reduce family's units run their two products and their atomics one after the other, which this
-    // bandwidth model does not see: measured on the smallest m = 128 shapes it is 5-35 % optimistic
-    if (p.family == FFUSE_FAMILY_REDUCE) t->t_pred *= 1.25;
+    // The reduce family's units run their two products and their atomics one after the other, which this bandwidth
+    // model does not see.  (Measured 0.65-1.1 of this: it errs to the far side, because these sums depend on the order
+    // in which the units arrive -- it is for what is clearly faster so, 75 x 128 x 10248 x 128 14 us against 18.)
+    if (p.family == FFUSE_FAMILY_REDUCE) t->t_pred *= 1.1;
     if (p.family == FFUSE_FAMILY_ROWS && t->feasible) {
         // The kernel is a weight stream through LDS at 64 flop per weight byte: per chunk a CU pulls the chunk's
         // weights through its load path, as long as the chunk's matrix instructions take.  Fitted on the device
         // (row-block rounds x (chunks x chunk time + a fixed part per row block)): the fraction of the matrix peak
-        // a chunk sustains grows with its size -- 0.36 for K = N2 = 512 (8.4 Mflop per chunk: 32768 x 512 x 4096 x 512
+        // a chunk sustains grows with its size -- kRowsEffSmall for K = N2 = 512 (8.4 Mflop per chunk: 32768 x 512 x 4096 x 512
         // in 368 us), kRowsEff for K = N2 = 1024 (16.8 Mflop: 32768 x 1024 x 8192 x 1024 in 1056 us, x 1024 x 1024 in
         // 170) -- and every row block pays about 20 us on top (X into registers, the ring primed again after the
         // output stores, the output block stored; the first one also the kernel's start: 120 KB of LDS, a long
@@ -482,7 +481,7 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         rows_geometry(p, gated, M, K, N1, N2, &rg);
         const double chunk_flops = 2.0 * 64.0 * 64.0 * (64.0 * rg.nks + 128.0 * rg.nt2);
         const double small = 2.0 * 64.0 * 64.0 * 1024.0, big = 2.0 * small;
-        const double eff = std::min(kRowsEff, std::max(0.30, 0.36 + (kRowsEff - 0.36) * (chunk_flops - small) / (big - small)));
+        const double eff = std::min(kRowsEff, std::max(0.30, kRowsEffSmall + (kRowsEff - kRowsEffSmall) * (chunk_flops - small) / (big - small)));
         const double t_chunk = chunk_flops / (d.mfma_flops / d.cus * eff);
         t->t_mfma = cdiv(cdiv(m, 64.0), d.cus) * (cdiv(n1, 64.0) * t_chunk + 20e-6);
         t->t_pred = std::max({t->t_mfma, t->t_l2, t->t_fabric, t->t_hbm}) + d.launch_s;
@@ -494,55 +493,64 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         // rather than by HBM; every item also pays ~3 us of pipeline fill and epilogue.  A
         // weight slice is fetched once per XCD patch of `raster` row blocks: the first fetch
         // comes from HBM, repeats (and the rows, once per slice group) from the Infinity Cache.
-        // Fixed: launch, one device-wide barrier, finalize (~13 us).
+        // Fixed: launch and barrier 7.5 us, and 2.25 for the launch that sums the planes.
+        // The constants of this model and of the small row blocks' were fitted together on every plan of 4707 measured
+        // shapes (FFN 1-32768 rows, widths 128-8192, and 3x3 chains; 30 plans each): the plan ranked first is 0.5 % behind
+        // the best measured one on average; predictions of plans worth running average 2 % high and scatter by 8 %.
         TwoPhaseGeometry sg;
         two_phase_geometry(p, gated, M, N1, N2, &sg);
         const double bh1 = sg.bh1;
         // a workgroup keeps a fixed number of bytes in flight, split between its row tile and its
-        // weight tile in proportion to their widths: ~50 GB/s in all, of which the weights' share
-        // (and never more than ~30 GB/s: three K steps of loads against a loaded memory latency)
-        // the LDS-direct loop's eight-stage ring holds about a third more
+        // weight tile in proportion to their widths: ~44 GB/s in all, 53 with the LDS-direct loop's
+        // deep ring, and never more than 42 (53 staged) of weights.  Weights that the memory-side cache kept from
+        // call to call (up to 90 MB; the measured calls took three sets of operands in turn) came 1.8 times as fast:
+        // without that, 32-row plans for 16-90 MB of weights were predicted 20-30 % high, those for more within 5 %.
         const bool deep = sg.bk == 32 && sg.bm < 256;
         // (the second phase's ring has eight stages only for 32-row blocks)
         const bool deep2 = deep && sg.bm == 32;
-        const double wg_all = deep ? 65e9 : 50e9, wg_cap = deep ? 40e9 : 30e9;
-        const double wg_all2 = deep2 ? 65e9 : 50e9, wg_cap2 = deep2 ? 40e9 : 30e9;
+        const double b1 = e * g * k * n1, b2 = e * n1 * n2;
+        const double warm = b1 + b2 <= 90e6 ? 1.77 : 1.0;
+        const double wg_all = warm * (deep ? 52.8e9 : 43.5e9), wg_cap = warm * (deep ? 41.8e9 : 52.9e9);
+        const double wg_all2 = warm * (deep2 ? 52.8e9 : 43.5e9), wg_cap2 = warm * (deep2 ? 41.8e9 : 52.9e9);
         const double per_wg1 = std::min(wg_cap, wg_all * (g * bh1) / (sg.bm + g * bh1)), per_wg2 = std::min(wg_cap2, wg_all2 * 256.0 / (sg.bm + 256.0));
         const double mb = cdiv(m, sg.bm), patches = cdiv(mb, sg.raster);
         const double n_s = cdiv(n1, bh1), ncb = cdiv(n2, 256);
         const double items1 = mb * n_s, items = mb * ncb * sg.splits;
-        const double b1 = e * g * k * n1, b2 = e * n1 * n2;
         const double cols_per_patch = std::max(1.0, 32.0 / std::min(mb, (double)sg.raster));
         const double re1 = b1 * (patches - 1.0) + e * m * k * std::max(0.0, n_s / cols_per_patch / 8.0 - 1.0);
         const double re2 = b2 * (patches - 1.0) + e * m * n1 * std::max(0.0, ncb / cols_per_patch / 8.0 - 1.0) + e * m * n1;
-        // pipeline fill and epilogue per item: the LDS-direct loop primes its ring faster (measured on the m = 128 tables)
-        const double per_item = (sg.bk == 32 && sg.bm < 256) ? 1.5e-6 : 3e-6;
+        // pipeline fill and epilogue per item: the LDS-direct loop primes its ring faster; the second phase's first
+        // weight tiles travel under the barrier
+        const double per_item = (sg.bk == 32 && sg.bm < 256) ? 0.8e-6 : 7.8e-6, per_item2 = 2.56e-6;
         // weights streamed with the non-temporal hint are not kept for the next row block: each streams its own copy
         const double copies = (weights_streamed(dtype, gated, K, N1, N2) && sg.bm < 256) ? mb : 1.0;
-        const double t1 = copies * b1 / std::min(d.hbm_bw, std::min(items1, (double)d.cus) * per_wg1) + re1 / d.fabric_bw + per_item * cdiv(items1, d.cus);
-        const double t2 = copies * b2 / std::min(d.hbm_bw, std::min(items, (double)d.cus) * per_wg2) + re2 / d.fabric_bw + per_item * cdiv(items, d.cus);
+        const double t1 = copies * b1 / std::min(warm * d.hbm_bw, std::min(items1, (double)d.cus) * per_wg1) + re1 / d.fabric_bw + per_item * cdiv(items1, d.cus);
+        const double t2 = copies * b2 / std::min(warm * d.hbm_bw, std::min(items, (double)d.cus) * per_wg2) + re2 / d.fabric_bw + per_item2 * cdiv(items, d.cus);
         // planes are written and read once; small transfers reach about half the cache rate
-        const double planes = sg.splits > 1 ? 2.0 * 4.0 * m * n2 * sg.splits / (0.5 * d.fabric_bw) : 0.0;
+        const double planes = sg.splits > 1 ? 2.0 * 4.0 * m * n2 * sg.splits / (0.615 * d.fabric_bw) : 0.0;
         // matrix-core time of each phase: items run one per CU, at the block GEMM's efficiency
         // for the item's tile shape
         const double f1 = d.mfma_flops * block_gemm_efficiency(sg.bm, g * bh1, sg.bk == 32 || sg.bm == 256) / d.cus;
         const double f2 = d.mfma_flops * block_gemm_efficiency(sg.bm, 256.0, sg.bk == 32 || sg.bm == 256) / d.cus;
-        // items are dealt statically, one per CU and round; a last, partly filled round is cheaper than a
-        // full one (fewer CUs share the power budget and the L2: its items run faster) -- fitted exponent.
-        // A lone, partly filled round lasts as long as one item all the same: 0.1 instead of 0.6 (measured on
-        // 700 x 1024 x 4096 x 1024 and 300 x 2048 x 8192 x 2048: with 0.6 the plan of the widest tiles and
-        // fewest ranges was ranked first, 37 and 11 % behind the best; with 0.1 the best is first on both)
+        // Items are dealt statically, one per CU and round, and a partly filled round lasts nearly as long as a full one:
+        // a lone one of a third of the CUs 0.9 of it, the last of several 0.86 and up (fewer CUs share the L2 and the
+        // power budget: their items run faster).  256-row tiles run at the power limit and gain more: 0.75 and 0.75.
+        // (With the last of several priced low, at frac^0.6, 64-column slices that need a second round were taken for
+        // 128-column ones that need one: gated 308 x 3000 x 6688 x 3000, 159 items 87 us, 315 items 106; gated 128 x 2560 x
+        // 9728 x 2560 in 64-row blocks, 152 items 68 us, 304 items 85.)
+        const bool big_tile = sg.bm == 256;
         const auto rounds = [&](double n) {
             const double full = std::floor(n / d.cus), frac = n / d.cus - full;
-            return full + (frac > 0.0 ? std::pow(frac, full > 0.0 ? 0.6 : 0.1) : 0.0);
+            if (frac <= 0.0) return full;
+            if (full == 0.0) return std::pow(frac, big_tile ? 0.262 : 0.0905);
+            return full + (big_tile ? 0.752 + 0.248 * std::pow(frac, 3.37) : 0.863 + 0.137 * std::pow(frac, 0.319));
         };
         // the efficiencies above were measured on items whose inner loop runs over 4096: they contain those items'
-        // ring fill and epilogue (about 10 us of a 256-row item, a tenth of it).  An item with a shorter loop
+        // ring fill and epilogue (about 7 us of a 256-row item).  An item with a shorter loop
         // pays the same fixed part on less work: the part the calibration does not already contain is added.
-        // (128-row items: 3.5 us, fitted on 32768 x 512 x 4096 x 512 and 65536 x 256 x 2048 x 256, where the model was 25-40 % optimistic)
-        const double item_fixed = sg.bm == 256 ? 10e-6 : (sg.bm == 128 ? 3.5e-6 : 0.0);
+        const double item_fixed = sg.bm == 256 ? 7.05e-6 : (sg.bm == 128 ? 2.92e-6 : 1.35e-6);
         const auto short_loop = [&](double loop) { return item_fixed * std::max(0.0, 1.0 - loop / 4096.0); };
-        const double m1 = (2.0 * sg.bm * bh1 * g * k / f1 + short_loop(k)) * rounds(items1);
+        const double m1 = (2.0 * sg.bm * bh1 * g * k / f1 + short_loop(k) * (gated ? 0.715 : 1.0)) * rounds(items1);
         const double m2 = (2.0 * sg.bm * 256.0 * sg.ksplit / f2 + short_loop(sg.ksplit)) * rounds(items);
         t->workgroups = d.cus;
         // weights (and their repeats per patch), X once and its repeats, the intermediate written through and read
@@ -551,10 +559,7 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
                           (sg.splits > 1 ? 2.0 * 4.0 * m * n2 * sg.splits : 0.0);
         t->t_hbm = t1 + t2;
         t->t_mfma = m1 + m2;
-        // launch, barrier, pipeline fills: 13 us.  (Where the barrier is per group the kernel is 2-3 us faster, but
-        // crediting that moved the boundary to the reduce family the wrong way on the smallest shapes -- 196 x 256 x
-        // 1024 x 256: reduce 13 us, two-phase 20 us, predicted 16.7 and 16.6 -- so the constant stays as fitted.)
-        t->t_pred = std::max(t1, m1) + std::max(t2, m2) + planes + 13e-6;
+        t->t_pred = std::max(t1, m1) + std::max(t2, m2) + planes + (sg.splits > 1 ? 9.74e-6 : 7.49e-6);
     }
 }
 
@@ -691,12 +696,15 @@ bool choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1
     }
     *out = r.front().plan;
     if (objective != FFUSE_OBJECTIVE_BYTES) {
-        // time objective: a near-tie goes to the schedule that keeps the traffic on the chip -- a plan predicted
-        // within 6 % of the fastest whose bytes between the L2s and the fabric are at most half of its
+        // time objective: a near-tie goes to the schedule that keeps the intermediate on the chip -- a rows plan predicted
+        // within 6 % of the fastest whose bytes between the L2s and the fabric are at most half of its.  (Between plans
+        // of one family the prediction already counts those bytes; among them the rule took gated 4023 x 256 x 1080 x 256 from
+        // 128- to 256-row tiles, 34 -> 47 us.)
         ffuse_traffic_t tb;
         traffic_model(*out, dtype, gated, M, K, N1, N2, &tb);
         for (const RankedPlan& c : r) {
             if (c.t_pred > 1.06 * r.front().t_pred) break;
+            if (c.plan.family != FFUSE_FAMILY_ROWS) continue;
             ffuse_traffic_t t;
             traffic_model(c.plan, dtype, gated, M, K, N1, N2, &t);
             if (t.feasible && t.fabric_bytes <= 0.5 * tb.fabric_bytes) { *out = c.plan; tb = t; }

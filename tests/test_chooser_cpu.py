@@ -258,3 +258,77 @@ def test_the_shipped_plan_table_loads_and_every_entry_is_runnable():
         assert ms_c == 0.0
     finally:
         ff.ffuse_plan_table_clear()
+
+
+# Measured on an MI355X, us per call, back to back on rotating operands: (shape, type, gated, {(family, bm, bh, bk, splits, raster): us}).
+# The plans that three models of this chooser ranked first, the best measured one and two others of 30 each.
+MEASURED = [
+    ((128, 2560, 9728, 2560), ff.DT_BF16, True, {(5, 64, 128, 32, 8, 2): 68.5, (5, 64, 64, 32, 8, 2): 85.1,
+      (5, 128, 64, 32, 16, 1): 68.3, (5, 64, 128, 32, 4, 2): 82.4, (5, 64, 64, 64, 8, 2): 100.2}),
+    ((128, 1536, 8960, 1536), ff.DT_BF16, True, {(5, 64, 128, 32, 16, 2): 36.3, (5, 64, 64, 32, 16, 2): 42.3,
+      (5, 64, 128, 32, 8, 2): 35.0, (5, 128, 128, 32, 32, 1): 45.5, (5, 128, 128, 64, 16, 1): 51.9}),
+    ((2551, 2792, 896, 2792), ff.DT_F16, True, {(5, 128, 128, 32, 1, 4): 57.3, (5, 128, 64, 32, 1, 4): 73.7,
+      (5, 128, 128, 32, 2, 4): 78.5}),
+    ((308, 3000, 6688, 3000), ff.DT_F16, True, {(5, 128, 128, 32, 4, 2): 87.4, (5, 128, 64, 32, 4, 2): 105.7,
+      (5, 128, 128, 64, 16, 2): 117.7, (5, 128, 64, 64, 8, 2): 130.1}),
+    ((137, 3200, 10048, 3200), ff.DT_F16, True, {(5, 128, 128, 32, 8, 2): 76.4, (5, 128, 64, 32, 8, 2): 89.5,
+      (5, 128, 128, 64, 16, 2): 99.6, (5, 256, 128, 32, 8, 1): 111.0}),
+    ((384, 1896, 5576, 1896), ff.DT_BF16, False, {(5, 128, 128, 32, 4, 2): 50.3, (5, 128, 64, 32, 8, 2): 58.9,
+      (5, 128, 128, 32, 8, 2): 47.1, (5, 128, 256, 32, 16, 2): 61.9, (5, 128, 64, 64, 8, 2): 69.6}),
+    ((5573, 1008, 1344, 1008), ff.DT_BF16, False, {(5, 128, 128, 32, 1, 4): 49.2, (5, 128, 256, 32, 1, 4): 57.5,
+      (5, 128, 128, 32, 2, 4): 67.9, (5, 128, 256, 32, 2, 4): 73.7}),
+    ((71, 1408, 9416, 1408), ff.DT_BF16, True, {(5, 64, 128, 32, 16, 2): 32.5, (5, 64, 64, 32, 16, 2): 38.0,
+      (5, 64, 128, 32, 4, 2): 41.5, (5, 128, 64, 64, 8, 1): 48.1}),
+    ((812, 2800, 2432, 2800), ff.DT_BF16, True, {(5, 128, 128, 32, 1, 4): 66.2, (5, 128, 64, 32, 2, 4): 77.2,
+      (5, 128, 128, 32, 2, 4): 61.1, (5, 128, 128, 64, 1, 4): 83.5, (5, 128, 128, 64, 4, 4): 84.6}),
+    ((1382, 2968, 9416, 2968), ff.DT_F16, False, {(5, 256, 256, 32, 2, 4): 209.3, (5, 128, 256, 32, 2, 4): 256.9,
+      (5, 128, 128, 32, 1, 4): 284.6, (5, 128, 64, 32, 4, 4): 312.1}),
+    ((2662, 3120, 10608, 3120), ff.DT_BF16, False, {(5, 256, 256, 32, 1, 4): 393.4, (5, 128, 256, 32, 1, 4): 479.7,
+      (5, 128, 128, 32, 1, 4): 526.9, (5, 128, 64, 32, 2, 4): 576.5}),
+    ((711, 3328, 13136, 3328), ff.DT_BF16, False, {(5, 256, 256, 32, 4, 2): 173.0, (5, 128, 256, 32, 4, 4): 210.7,
+      (5, 256, 256, 32, 2, 2): 229.7, (5, 128, 128, 64, 4, 4): 244.8}),
+    ((1908, 2680, 14760, 2680), ff.DT_BF16, True, {(5, 256, 128, 32, 2, 8): 480.6, (5, 128, 128, 32, 2, 4): 580.6,
+      (5, 256, 128, 32, 2, 4): 490.2, (5, 128, 128, 64, 2, 4): 602.8, (5, 128, 64, 32, 1, 4): 713.5}),
+    ((1666, 1160, 13576, 1160), ff.DT_BF16, True, {(5, 256, 128, 32, 4, 4): 208.2, (5, 128, 128, 32, 4, 4): 245.3,
+      (5, 256, 128, 32, 2, 4): 264.1, (5, 128, 64, 32, 4, 4): 299.9}),
+    ((8369, 776, 2888, 776), ff.DT_BF16, False, {(5, 256, 256, 32, 1, 4): 132.7, (5, 128, 256, 32, 1, 4): 146.8,
+      (5, 128, 64, 32, 1, 4): 175.0, (5, 128, 128, 64, 2, 4): 183.6}),
+    ((578, 1024, 4608, 1024), ff.DT_BF16, True, {(5, 128, 128, 32, 2, 4): 52.2, (5, 128, 128, 32, 8, 4): 39.3,
+      (5, 128, 64, 64, 8, 4): 54.5, (5, 128, 64, 64, 4, 4): 58.6}),
+    ((641, 1080, 3944, 1080), ff.DT_BF16, True, {(5, 128, 128, 32, 2, 4): 51.9, (5, 128, 128, 32, 8, 4): 42.6,
+      (5, 128, 128, 64, 16, 4): 57.4, (5, 128, 128, 64, 2, 4): 61.5}),
+    ((10918, 256, 1152, 256), ff.DT_BF16, False, {(5, 256, 256, 32, 1, 4): 53.3, (5, 128, 256, 32, 1, 4): 41.8,
+      (5, 128, 128, 64, 1, 4): 52.8, (5, 128, 64, 64, 2, 4): 62.4}),
+    ((128, 384, 1536, 384), ff.DT_BF16, False, {(5, 64, 64, 32, 16, 2): 16.4, (1, 16, 64, 32, 24, 1): 10.8,
+      (1, 32, 64, 32, 16, 1): 14.6, (5, 64, 64, 32, 32, 2): 16.1}),
+    ((231, 512, 1024, 512), ff.DT_BF16, False, {(5, 128, 64, 32, 8, 2): 20.2, (1, 16, 64, 32, 8, 1): 12.5,
+      (1, 32, 64, 32, 8, 1): 15.2, (1, 16, 64, 32, 4, 1): 17.0}),
+    ((4, 7040, 15616, 7040), ff.DT_BF16, True, {(5, 32, 128, 32, 8, 1): 127.4, (5, 32, 128, 64, 16, 1): 149.5,
+      (5, 32, 128, 32, 2, 1): 173.8}),
+    ((126, 1920, 5136, 1920), ff.DT_F16, False, {(5, 64, 64, 32, 8, 2): 27.3, (5, 64, 64, 32, 16, 2): 28.2,
+      (5, 64, 64, 64, 16, 2): 36.8, (5, 128, 64, 32, 4, 1): 40.5}),
+    ((4096, 4096, 16384, 4096), ff.DT_BF16, False, {(5, 256, 256, 32, 1, 4): 867.2, (5, 128, 128, 32, 1, 4): 1076.3}),
+    ((2048, 4096, 11008, 4096), ff.DT_BF16, True, {(5, 256, 128, 32, 2, 4): 469.2, (5, 128, 64, 32, 1, 4): 607.4,
+      (5, 128, 64, 32, 2, 4): 633.6}),
+    ((128, 4096, 11008, 4096), ff.DT_BF16, True, {(5, 64, 128, 32, 8, 2): 90.3, (5, 128, 64, 32, 16, 1): 87.4,
+      (5, 64, 128, 32, 32, 2): 108.6, (5, 64, 128, 32, 2, 2): 128.1}),
+    ((142, 1152, 1664, 1152), ff.DT_BF16, True, {(5, 128, 64, 32, 8, 2): 28.4, (1, 16, 64, 32, 26, 1): 23.3,
+      (5, 128, 128, 32, 16, 2): 32.5, (5, 128, 64, 64, 8, 2): 34.0}),
+]
+
+
+def test_the_models_choice_against_measured_plans():
+    """Regression set of the chooser: its choice is among the measured plans and within 5 % of the best of them.
+    Predictions scatter by 8 % round the measured time where a plan is worth running; the worst of this set is 1.46 off
+    (a plan that measures 25 % behind).  (A model that priced a lone partial round of items as a whole
+    one, but the last of two rounds low, lost 10-29 % on the first fifteen.)"""
+    for (shape, dt, gated, plans) in MEASURED:
+        act = 3 if gated else 2
+        c = ff.ffuse_choose_plan(dt, act, gated, *shape)
+        key = (c.family, c.bm, c.bh, c.bk, c.splits, c.raster)
+        assert key in plans, (shape, gated, key)
+        assert plans[key] <= 1.05 * min(plans.values()), (shape, gated, key, plans)
+        for (family, bm, bh, bk, splits, raster), us in plans.items():
+            p = ff.make_plan(family, bm=bm, bh=bh, bn2=256, bk=bk, splits=splits, raster=raster)
+            t = ff.ffuse_traffic_model(p, dt, gated, *shape).t_pred * 1e6
+            assert us / 1.5 < t < 1.5 * us, (shape, gated, (family, bm, bh, bk, splits, raster), us, t)
