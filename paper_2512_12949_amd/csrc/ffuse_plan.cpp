@@ -322,7 +322,8 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->reduce_bytes = planes;
         t->hbm_bytes = t->q_min;
         t->lds_used = (gated ? 8.0 : 4.0) * dg.bm * 256.0 + dg.bm * 144.0;
-        t->acc_regs = 4.0 * dg.ng * dg.bm;
+        t->acc_regs = (double)dg.ng * dg.bm;
+        t->feasible = t->lds_used <= d.lds_bytes && t->acc_regs <= d.acc_regs;
         t->t_hbm = t->hbm_bytes / d.hbm_bw;
         t->t_fabric = t->fabric_bytes / d.fabric_bw;
         t->t_l2 = t->l2_bytes / d.l2_bw;

@@ -332,3 +332,13 @@ def test_the_models_choice_against_measured_plans():
             p = ff.make_plan(family, bm=bm, bh=bh, bn2=256, bk=bk, splits=splits, raster=raster)
             t = ff.ffuse_traffic_model(p, dt, gated, *shape).t_pred * 1e6
             assert us / 1.5 < t < 1.5 * us, (shape, gated, (family, bm, bh, bk, splits, raster), us, t)
+
+
+def test_accumulators_of_the_small_row_blocks():
+    """bm rows x 256 ng output columns of fp32 over 256 lanes: bm ng registers per lane, within the device's 256."""
+    for N2, ng in ((8, 1), (256, 1), (264, 2), (512, 2), (1000, 4), (2048, 8)):
+        for bm in (16, 32):
+            if bm == 32 and N2 > 512:
+                continue
+            t = ff.ffuse_traffic_model(ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=2), ff.DT_BF16, False, 100, 512, 512, N2)
+            assert t.feasible and t.acc_regs == bm * ng <= 256, (N2, bm, t.acc_regs)
