@@ -441,19 +441,23 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
     } else {  // fp32 path
         const double units = cdiv(m, 16) * cdiv(n1, 64);
         t->workgroups = (int)units;
-        mfma_flops = 256 * 128.0 * 2.4e9;  // fp32 FMA rate, not matrix cores
+        mfma_flops = d.cus * 256.0 * 2.4e9;  // the fp32 matrix instructions
+        // the start and the end of the grid cost half a chip's worth of workgroups
+        waves = 1.0 + 0.5 * d.cus / units;
         t->l2_bytes = units * e * (16 * k + g * k * 64 + 64 * n2);
         t->fabric_bytes = t->l2_bytes / 8.0;
         t->reduce_bytes = 4.0 * m * n2 * cdiv(n1, 64);
         t->hbm_bytes = t->q_min;
-        t->lds_bytes = t->flops * 2.0;
+        t->lds_bytes = units * (g * 32768.0 + 8192.0 + 128.0 * n2);   // partial tiles, H, output blocks on their way to the atomics
     }
     // the reduce family's 4x1 wave layout and 128-row tiles run the matrix cores at ~2/3 of the
     // 256x256 main loop's efficiency (measured on the m = 128 shapes)
-    const double eff = p.family == FFUSE_FAMILY_SCALAR ? 1.0 : (p.family == FFUSE_FAMILY_REDUCE ? 0.67 * d.mfma_eff : d.mfma_eff);
+    // (fp32: 0.45 of the matrix rate; measured 0.29-0.54 from 512 rows up, more the longer K and where gated)
+    const double eff = p.family == FFUSE_FAMILY_SCALAR ? 0.45 : (p.family == FFUSE_FAMILY_REDUCE ? 0.67 * d.mfma_eff : d.mfma_eff);
     t->t_mfma = padded * waves / (mfma_flops * eff);
     // the reduce family's kernel streams weights at well under half the HBM rate (measured at M <= 16)
-    t->t_hbm = t->hbm_bytes / (p.family == FFUSE_FAMILY_REDUCE ? 0.45 * d.hbm_bw : d.hbm_bw);
+    // (so does the fp32 kernel: 16 x 4096 x 11008 x 4096, 361 MB, 168 us)
+    t->t_hbm = t->hbm_bytes / (p.family == FFUSE_FAMILY_REDUCE ? 0.45 * d.hbm_bw : p.family == FFUSE_FAMILY_SCALAR ? 0.4 * d.hbm_bw : d.hbm_bw);
     t->t_fabric = t->fabric_bytes / d.fabric_bw;
     t->t_l2 = t->l2_bytes / d.l2_bw;
     t->t_lds = t->lds_bytes / d.lds_bw;
@@ -461,7 +465,8 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
     double worst = std::max({t->t_mfma, t->t_hbm, t->t_fabric, t->t_l2, t->t_lds});
     // atomics of one unit are issued after its matrix work: with a single round of units
     // nothing overlaps them; with several rounds about half does
-    const double overlap = (t->workgroups <= d.cus) ? 0.0 : 0.5;
+    // (fp32: they travel under the next column block)
+    const double overlap = p.family == FFUSE_FAMILY_SCALAR ? 1.0 : (t->workgroups <= d.cus) ? 0.0 : 0.5;
     worst = std::max(worst, t->t_reduce) + (1.0 - overlap) * std::min(worst, t->t_reduce);
     const double launches = 2.0;  // main kernel + finalise / second GEMM / zero fill
     t->t_pred = worst + launches * d.launch_s;

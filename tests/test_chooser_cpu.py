@@ -342,3 +342,19 @@ def test_accumulators_of_the_small_row_blocks():
                 continue
             t = ff.ffuse_traffic_model(ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=2), ff.DT_BF16, False, 100, 512, 512, N2)
             assert t.feasible and t.acc_regs == bm * ng <= 256, (N2, bm, t.acc_regs)
+
+
+def test_fp32_predictions_against_measured_calls():
+    """fp32 mode on an MI355X, us per call: one row to 8192, gated and not (a prediction within a factor 1.5)."""
+    plain = {(16, 256, 1024, 256): 8.1, (128, 256, 1024, 256): 10.1, (256, 512, 2048, 512): 29.3, (512, 512, 2048, 512): 46.8,
+             (2048, 512, 2048, 512): 151.6, (8192, 256, 1024, 256): 152.8, (512, 1024, 4096, 1024): 146.8, (2048, 1024, 4096, 1024): 484.6,
+             (16, 4096, 11008, 4096): 168.2, (128, 64, 256, 64): 7.7, (64, 1000, 264, 1000): 18.3, (333, 1016, 2744, 1016): 99.7,
+             (1, 512, 2048, 512): 10.6}
+    gated = {(128, 256, 1024, 256): 13.3, (512, 512, 2048, 512): 55.8, (2048, 512, 2048, 512): 174.7, (2048, 1024, 4096, 1024): 605.6,
+             (16, 4096, 11008, 4096): 229.7, (128, 64, 256, 64): 7.7}
+    for table, g in ((plain, False), (gated, True)):
+        for shape, us in table.items():
+            p = ff.ffuse_choose_plan(ff.DT_F32, 2, g, *shape)
+            t = ff.ffuse_traffic_model(p, ff.DT_F32, g, *shape).t_pred * 1e6
+            print(shape, g, us, round(t, 1))
+            assert us / 1.5 < t < 1.5 * us, (shape, g, us, t)
