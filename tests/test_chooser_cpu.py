@@ -260,6 +260,23 @@ def test_the_shipped_plan_table_loads_and_every_entry_is_runnable():
         ff.ffuse_plan_table_clear()
 
 
+def test_no_shipped_entry_is_slower_than_the_models_best_plan():
+    """A measured entry overrides the model: recorded times lie within 25 % of what the model expects of its best plan
+    (predictions scatter by 8 %), or the table predates a faster kernel and has to be measured again."""
+    from paper_2512_12949_amd import inputs
+    ff.ffuse_plan_table_clear()
+    try:
+        ff.ffuse_load_shipped_plans()
+        for name in ["gpt", "llama", "large", "decode16", "decode64"] + [f"G{i}" for i in range(1, 11)] + [f"S{i}" for i in range(1, 9)]:
+            w = inputs.WORKLOADS[name]
+            dt = ff.DTYPE_CODE[w.dtype]
+            _, ms = ff.ffuse_plan_lookup(dt, w.act, w.gated, w.M, w.K, w.N1, w.N2)
+            _, best = ff.ffuse_rank_plans(dt, w.act, w.gated, w.M, w.K, w.N1, w.N2)[0]
+            assert 0.0 < ms * 1e-3 < 1.25 * best, (name, ms, best)
+    finally:
+        ff.ffuse_plan_table_clear()
+
+
 # Measured on an MI355X, us per call, back to back on rotating operands: (shape, type, gated, {(family, bm, bh, bk, splits, raster): us}).
 # The plans that three models of this chooser ranked first, the best measured one and two others of 30 each.
 MEASURED = [
