@@ -18,7 +18,7 @@
 // about K / (128 DEPTH) round trips.  Against that, operands are re-read from L2 by every row block.
 //
 // Measured (us, the best of the other plans -> this): 3x3 chains 196 pixels x 2304 x 256 x 1024 41 -> 16, 49 x 4608 x
-// 512 x 2048 47 -> 25, 6272 x 576 x 64 x 256 21 -> 8; 128 x 384 x 1536 x 384 17.4 -> 12.0; 3136 x 64 x 256 x 64
+// 512 x 2048 47 -> 25, 6272 x 576 x 64 x 256 21 -> 8; 128 x 384 x 1536 x 384 17.4 -> 10.8; 3136 x 64 x 256 x 64
 // 8.9 -> 7.0.  It loses from about 1.5 Gflop on (200 x 1024 x 4096 x 1024: 28 against 34).  Issuing a slice's first W2
 // loads a slice earlier was 3-5 % slower: the walk is bound by issue, not by the wait for those loads.
 //
