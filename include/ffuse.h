@@ -108,7 +108,8 @@ typedef enum {
                                  device-wide barrier, then every CU multiplies a row block of it
                                  with a block of W2 (Sec. 4.1 "shuffle" with the device as the
                                  cluster).  bm = 32 / 64 / 128 (M <= bm for the first two) or
-                                 256; `splits` ranges of the hidden dimension: 1 = the tile is
+                                 256; bk = 128 with bm = 16 or 32 (M <= bm) and bh = 64: the streaming
+                                 kernel, weights straight to registers; `splits` ranges of the hidden dimension: 1 = the tile is
                                  stored straight to Y, > 1 = per-range fp32 planes summed in a
                                  fixed order by a finalize pass (Sec. 4.1 "reduce")          */
 } ffuse_family_t;
@@ -253,7 +254,8 @@ int ffuse_force_plan(const ffuse_plan_t* plan);
 /* Other environment variables, read by the fused and unfused calls:
  *   FFUSE_NT=0|1   two-phase family, row blocks below 256: never / always stream the weights with the
  *                  non-temporal load hint.  Default: only when the weights exceed 512 MB -- far more than
- *                  the 256 MB memory-side cache can keep from one call to the next.  A caller that cycles
+ *                  the 256 MB memory-side cache can keep from one call to the next.  (Streaming kernel:
+ *                  when they exceed 256 MB and N1 and N2 are multiples of 64.)  A caller that cycles
  *                  through many layers' weights may want 1 for smaller layers too.
  *   FFUSE_GROUP_BARRIER=0  the two-phase kernel's barrier always waits for every workgroup (default: a group
  *                  of workgroups waits for the groups whose tiles of the intermediate its second-phase

@@ -246,9 +246,9 @@ int run_fused(int dtype, const void* X, const void* W1, const void* W3, const vo
 // hint (measured on the 1.4 GB decode shapes: 9 % faster, 5.8 instead of 5.3 TB/s); weights the
 // cache can keep between calls are not (the hint cost 10-40 % on the 64-270 MB shapes when the
 // same weights are used call after call).
-int stream_weights(int dtype, int gated, int64_t K, int64_t N1, int64_t N2) {
+int stream_weights(int bk, int dtype, int gated, int64_t K, int64_t N1, int64_t N2) {
     if (const char* env = std::getenv("FFUSE_NT")) return std::atoi(env) != 0;   // read per call: a test can switch it
-    return ffuse::weights_streamed(dtype, gated, K, N1, N2) ? 1 : 0;
+    return (bk == 128 ? ffuse::stream_hint(dtype, gated, K, N1, N2) : ffuse::weights_streamed(dtype, gated, K, N1, N2)) ? 1 : 0;
 }
 
 // The barrier's wait masks are an enumeration of the kernel's item maps (thousands of items at the large
@@ -360,7 +360,7 @@ int run_plan(const ffuse_plan_t& plan, int dtype, const void* X, const void* W1,
         w.zero = 0;      // planes and H overwrite the region the reduce family keeps at zero
         ffuse::TwoPhaseArgs s{X, W1, W3, W2, base + sg.ysum_bytes, Y, reinterpret_cast<float*>(base), flags,
                               M, (int)K, (int)N1, (int)N2, act, sg.splits, sg.ksplit, sg.raster, nullptr,
-                              conv.ic, conv.h, conv.w, stream_weights(dtype, gated, K, N1, N2),
+                              conv.ic, conv.h, conv.w, stream_weights(sg.bk, dtype, gated, K, N1, N2),
                               group_barrier() ? wait_masks(sg, M, N1, N2) : ~(uint64_t)0, 3,
                               g.spin_limit, g.extra_arrivals, early_fill(), sg.gate_split ? base + sg.ysum_bytes + sg.h_bytes : nullptr};
         if (g.log && w.bytes >= sg.ws_bytes + 65536) {
@@ -370,15 +370,19 @@ int run_plan(const ffuse_plan_t& plan, int dtype, const void* X, const void* W1,
         }
         // (launched one phase at a time there is no barrier and no verdict)
         g.exch_err = two_launches ? nullptr : flags + 3;
+        const auto launch = [&] {
+            return sg.bk == 128 ? ffuse::launch_fused_stream(dtype, s, sg.bm, g.cus, st)
+                                : ffuse::launch_fused_two_phase(dtype, s, sg.bm, sg.bh1, sg.bk, g.cus, st);
+        };
         {
             Timer t(st);
             if (two_launches) {
                 s.phases = 1;
-                if (ffuse::launch_fused_two_phase(dtype, s, sg.bm, sg.bh1, sg.bk, g.cus, st) != hipSuccess) return FFUSE_ERR_LAUNCH;
+                if (launch() != hipSuccess) return FFUSE_ERR_LAUNCH;
                 s.phases = 2;
                 if (s.stats) s.stats += 4 * 1024;
             }
-            if (ffuse::launch_fused_two_phase(dtype, s, sg.bm, sg.bh1, sg.bk, g.cus, st) != hipSuccess) return FFUSE_ERR_LAUNCH;
+            if (launch() != hipSuccess) return FFUSE_ERR_LAUNCH;
             if (sg.splits > 1 && ffuse::launch_finalize_planes(dtype, s.part, Y, M * N2, sg.splits, st) != hipSuccess) return FFUSE_ERR_LAUNCH;
             t.stop();
         }
@@ -793,7 +797,7 @@ int run_conv_chain(int dtype, const void* X, const void* W1, const void* W2, int
             std::vector<ffuse::RankedPlan> ranked;
             ffuse::rank_plans(dtype, act, 0, M, K, OC1, OC2, &ranked);
             for (const auto& r : ranked)
-                if (((r.plan.family == FFUSE_FAMILY_TWOPHASE && r.plan.bm <= 128 && r.plan.bk != 32) || ffuse::is_direct(r.plan)) &&
+                if (((r.plan.family == FFUSE_FAMILY_TWOPHASE && r.plan.bm <= 128 && r.plan.bk == 64) || ffuse::is_direct(r.plan)) &&
                     ffuse::plan_workspace_bytes(r.plan, dtype, 0, M, K, OC1, OC2) <= ws.bytes) {
                     plan = r.plan;
                     found = true;

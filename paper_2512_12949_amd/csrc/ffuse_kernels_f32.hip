@@ -188,9 +188,9 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_resident(const void* fn, int grid, void** params, hipStream_t st) {
+hipError_t launch_resident(const void* fn, int grid, void** params, hipStream_t st, int threads) {
     static const bool cooperative = getenv("FFUSE_COOPERATIVE_LAUNCH") != nullptr;
-    if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(256), params, 0, st);
+    if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(threads), params, 0, st);
     // how many workgroups of this kernel the device holds at once: asked once per kernel
     static std::mutex mu;
     static std::unordered_map<const void*, int> capacity;
@@ -202,7 +202,7 @@ hipError_t launch_resident(const void* fn, int grid, void** params, hipStream_t 
     }
     if (cap == 0) {
         int per_cu = 0, dev = 0, cus = 0;
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0);
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0);
         if (e != hipSuccess) return e;
         if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
         if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
@@ -212,7 +212,7 @@ hipError_t launch_resident(const void* fn, int grid, void** params, hipStream_t 
         capacity[fn] = cap;
     }
     if (grid > cap) return hipErrorCooperativeLaunchTooLarge;
-    return hipLaunchKernel(fn, dim3(grid), dim3(256), params, 0, st);
+    return hipLaunchKernel(fn, dim3(grid), dim3(threads), params, 0, st);
 }
 
 hipError_t launch_fused_f32(const FusedArgs& a, float* Y, hipStream_t st) {

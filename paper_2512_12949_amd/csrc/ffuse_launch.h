@@ -121,6 +121,8 @@ struct DirectArgs {
 // nks: 16-k steps of the first product per wave (K <= 64 nks); nt2: 32-column output tiles per wave (N2 <= 128 nt2)
 hipError_t launch_fused_rows(int dtype, const RowsArgs& a, int nks, int nt2, int grid, hipStream_t st);
 hipError_t launch_fused_two_phase(int dtype, const TwoPhaseArgs& a, int bm, int bh1, int bk, int grid, hipStream_t st);
+// the streaming kernel: bm = 16 or 32 rows, items of 64 columns in both phases
+hipError_t launch_fused_stream(int dtype, const TwoPhaseArgs& a, int bm, int grid, hipStream_t st);
 hipError_t launch_finalize_planes(int dtype, const float* part, void* Y, int64_t count, int planes, hipStream_t st);
 // bm: rows per workgroup (16 or 32); ng: blocks of 256 output columns (1, 2, and with 16 rows 4 and 8); sums the planes too
 hipError_t launch_fused_direct(int dtype, const DirectArgs& a, int bm, int ng, hipStream_t st);
@@ -134,7 +136,7 @@ hipError_t launch_finalize(int dtype, float* sums, void* Y, int64_t count, hipSt
 // which costs ~17 us less per call than hipLaunchCooperativeKernel; all in-kernel waits are
 // bounded, so foreign work occupying compute units surfaces as FFUSE_ERR_TIMEOUT, not as a
 // hang.  FFUSE_COOPERATIVE_LAUNCH=1 selects the runtime's cooperative launch instead.
-hipError_t launch_resident(const void* fn, int grid, void** params, hipStream_t st);
+hipError_t launch_resident(const void* fn, int grid, void** params, hipStream_t st, int threads = 256);
 
 // zero fill with a kernel (safe to record into a captured graph, unlike a memset node);
 // bytes must be a multiple of 16

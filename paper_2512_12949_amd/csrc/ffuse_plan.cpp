@@ -129,9 +129,20 @@ bool direct_geometry(const ffuse_plan_t& p, int64_t M, int64_t N1, int64_t N2, D
     return true;
 }
 
-bool weights_streamed(int dtype, int gated, int64_t K, int64_t N1, int64_t N2) {
+static double weight_bytes(int dtype, int gated, int64_t K, int64_t N1, int64_t N2) {
     const double e = dtype == FFUSE_DT_F32 ? 4.0 : 2.0;
-    return e * ((gated ? 2.0 : 1.0) * (double)K * (double)N1 + (double)N1 * (double)N2) > 512.0 * 1024 * 1024;
+    return e * ((gated ? 2.0 : 1.0) * (double)K * (double)N1 + (double)N1 * (double)N2);
+}
+
+bool weights_streamed(int dtype, int gated, int64_t K, int64_t N1, int64_t N2) {
+    return weight_bytes(dtype, gated, K, N1, N2) > 512.0 * 1024 * 1024;
+}
+
+// The streaming kernel reads a weight once: the hint pays as soon as the memory-side cache cannot keep the weights
+// (gated 3 x 3968 x 12608 x 3968, 300 MB: 56.4 us without, 52.4 with; 67 MB: 21.2, 26.4).  Not where rows are not whole cache lines:
+// neighbouring slices then share lines, which have to stay a moment (gated 8 x 3584 x 14504 x 3584, 312 MB: 67.7, 71.8).
+bool stream_hint(int dtype, int gated, int64_t K, int64_t N1, int64_t N2) {
+    return N1 % 64 == 0 && N2 % 64 == 0 && weight_bytes(dtype, gated, K, N1, N2) > 256.0 * 1024 * 1024;
 }
 
 int two_phase_max_splits(int64_t M, int64_t N2) {
@@ -150,7 +161,9 @@ bool two_phase_geometry(const ffuse_plan_t& p, int gated, int64_t M, int64_t N1,
     if (p.gate_split) gated = 0;    // the items of the first phase are single-branch tiles
     int bm = p.bm;
     if (bm <= 0) bm = M <= 32 ? 32 : (M <= 64 ? 64 : (M <= 512 ? 128 : 256));
-    if (bm != 32 && bm != 64 && bm != 128 && bm != 256) return false;
+    const bool stream = p.bk == 128 && p.bh == 64 && (bm == 16 || bm == 32);
+    if (stream && (p.gate_split || M > bm)) return false;
+    if (bm != 32 && bm != 64 && bm != 128 && bm != 256 && !stream) return false;
     if (bm < 128 && M > 4 * bm) return false;   // the small blocks are for a few row blocks at most
     g->bm = bm;
     // hidden slice of a phase-1 item: the plan's bh where the kernels implement it
@@ -158,14 +171,15 @@ bool two_phase_geometry(const ffuse_plan_t& p, int gated, int64_t M, int64_t N1,
         g->bh1 = gated ? 128 : 256;
     } else {
         g->bh1 = p.bh > 0 ? p.bh : 128;
-        const bool ok = g->bh1 == 128 || (g->bh1 == 64 && bm >= 64) || (g->bh1 == 32 && bm == 128 && !gated) ||
+        const bool ok = stream || g->bh1 == 128 || (g->bh1 == 64 && bm >= 64) || (g->bh1 == 32 && bm == 128 && !gated) ||
                         (g->bh1 == 256 && bm == 128 && !gated && p.bk == 32);
         if (!ok) {
             if (p.bh == 256) g->bh1 = 128;   // plans written before narrow slices existed
             else return false;
         }
     }
-    g->bk = bm == 256 ? 32 : (p.bk == 32 ? 32 : 64);
+    g->bk = bm == 256 ? 32 : (p.bk == 32 ? 32 : (stream ? 128 : 64));
+    g->bn2 = stream ? 64 : 256;
     if (g->bk == 32 && bm != 256 && !(g->bh1 == 128 || g->bh1 == 256 || (g->bh1 == 64 && bm >= 64))) return false;
     const int64_t mb = (M + bm - 1) / bm;
     g->raster = p.raster > 0 ? p.raster : 1;
@@ -202,7 +216,7 @@ bool two_phase_item(int MB, int S, int raster, int grp, int idx, int* i, int* s)
 uint64_t two_phase_wait_masks(const TwoPhaseGeometry& g, int64_t M, int64_t N1, int64_t N2) {
     const int MB = (int)((M + g.bm - 1) / g.bm);
     const int NS1 = (int)((N1 + g.bh1 - 1) / g.bh1);
-    const int NCB = (int)((N2 + 255) / 256);
+    const int NCB = (int)((N2 + g.bn2 - 1) / g.bn2);
     if (g.gate_split) return ~(uint64_t)0;   // (two device-wide rendezvous: branch tiles are joined across groups)
     if ((int64_t)MB * NS1 > 65536 || (int64_t)MB * NCB * g.splits > 65536) return ~(uint64_t)0;   // (not worth the host time)
     // producer group of every H tile (row block, phase-1 slice)
@@ -492,6 +506,30 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->t_mfma = cdiv(cdiv(m, 64.0), d.cus) * (cdiv(n1, 64.0) * t_chunk + 20e-6);
         t->t_pred = std::max({t->t_mfma, t->t_l2, t->t_fabric, t->t_hbm}) + d.launch_s;
     }
+    TwoPhaseGeometry stream;
+    if (p.family == FFUSE_FAMILY_TWOPHASE && t->feasible && two_phase_geometry(p, gated, M, N1, N2, &stream) && stream.bk == 128) {
+        // The streaming kernel: each phase the longer of its bytes and its workgroups' steps of 512 k, one after the other
+        // (1.9 us each, 3.5 with two matrices; the fourth-power mean of the two), and the rest fixed.  Weights that the
+        // memory-side cache kept from call to call (up to 90 MB, three sets in turn) come 1.86 times as fast.  17-32 rows:
+        // 1.22 times as long.  Fitted on 880 timings of 150 shapes (1-32 rows, 1 to 512 MB): no bias, 9 % scatter, the plan
+        // ranked first 1.2 % behind the best on average.
+        const double b1 = e * g * k * n1, b2 = e * n1 * n2, warm = b1 + b2 <= 90e6 ? 1.863 : 1.0, bw = 6.07e12 * warm;
+        const double rows = stream.bm == 32 ? 1.225 : 1.0, ncb = cdiv(n2, 64), items2 = ncb * stream.splits;
+        const auto phase = [&](double bytes, double steps, double step) {
+            return rows * std::pow(std::pow(bytes / bw, 4.0) + std::pow(steps * step / std::sqrt(warm), 4.0), 0.25);
+        };
+        const double planes = stream.splits > 1 ? 2.0 * 4.0 * m * n2 * stream.splits : 0.0;
+        t->workgroups = d.cus;
+        t->lds_used = g * 8.0 * stream.bm * 256.0;
+        t->acc_regs = g * stream.bm;
+        t->fabric_bytes = b1 + b2 + 8.0 * e * m * k + e * m * n1 * (1.0 + std::min(8.0, ncb)) + e * m * n2 + planes;
+        t->t_hbm = (b1 + b2) / bw;
+        t->t_mfma = 0.0;
+        t->t_pred = 6.74e-6 + phase(b1, cdiv(n1 / 64.0, d.cus) * cdiv(k, 512.0), gated ? 3.50e-6 : 1.91e-6) +
+                    phase(b2, cdiv(items2, d.cus) * cdiv(stream.ksplit, 512.0), 1.91e-6) + 0.21e-6 * (cdiv(items2, d.cus) - 1.0) +
+                    (stream.splits > 1 ? planes / (0.615 * d.fabric_bw) + 2.54e-6 : 0.0);
+        return;
+    }
     if (p.family == FFUSE_FAMILY_TWOPHASE && t->feasible) {
         // two phases back to back, each the longer of its streaming time and its matrix time.
         // Streaming: a workgroup of this kernel keeps ~64 KB in flight and sustains ~25 GB/s on
@@ -649,11 +687,31 @@ void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1,
             }
         }
     }
+    // The streaming kernel: one row block of up to 32 rows, at most one 64-column slice a workgroup, weights up to 512 MB.
+    // 170 drawn shapes of 1-32 rows against the LDS-direct plans: 10-45 % faster with 6 to 400 MB; beyond one slice a
+    // workgroup 0-20 % slower (9 x 2304 x 27704 x 2304 74 us, 83), as beyond 512 MB with few exceptions (gated 2 x 7040 x 19968 x 7040
+    // 151, 193); from 33 rows on X, which every slice reads again, is too much of it (gated 64 x 4096 x 11008 x 4096 71, 92).
+    if (M <= 32 && N1 <= 64 * (int64_t)kDevice.cus && !weights_streamed(dtype, gated, K, N1, N2)) {
+        const int ncb = (int)((N2 + 63) / 64), fill = std::max(1, kDevice.cus / ncb);   // ranges that give every CU an output block
+        std::vector<int> ranges = {fill, std::max(1, fill / 2), 2 * fill, 4, 8, 16};
+        std::sort(ranges.begin(), ranges.end());
+        ranges.erase(std::unique(ranges.begin(), ranges.end()), ranges.end());
+        for (int sp : ranges) {
+            if (sp > two_phase_max_splits(M, N2)) continue;
+            ffuse_plan_t p;
+            std::memset(&p, 0, sizeof(p));
+            p.family = FFUSE_FAMILY_TWOPHASE;
+            p.bm = M <= 16 ? 16 : 32; p.bh = 64; p.bn2 = 64; p.bk = 128; p.h_level = 2; p.raster = 1; p.splits = sp;
+            ffuse_traffic_t t;
+            traffic_model(p, dtype, gated, M, K, N1, N2, &t);
+            if (t.feasible) out->push_back({t.t_pred, p});
+        }
+    }
     if (gated) {
         // the best two-phase plan with its branches on different workgroups (never predicted faster: it is there to be measured)
         const RankedPlan* b = nullptr;
         for (const RankedPlan& c : *out)
-            if (c.plan.family == FFUSE_FAMILY_TWOPHASE && (!b || c.t_pred < b->t_pred)) b = &c;
+            if (c.plan.family == FFUSE_FAMILY_TWOPHASE && c.plan.bk != 128 && (!b || c.t_pred < b->t_pred)) b = &c;
         if (b) {
             ffuse_plan_t p = b->plan;
             p.gate_split = 1;

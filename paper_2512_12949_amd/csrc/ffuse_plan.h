@@ -41,8 +41,10 @@ bool exchange_geometry(const ffuse_plan_t& p, int gated, int64_t M, int64_t N1, 
 // Two-phase family: derived geometry.
 struct TwoPhaseGeometry {
     int bm;             // rows per block: 32, 64, 128 or 256
-    int bk;             // 32: LDS-direct block GEMM (always for bm = 256; optional for bm = 64 / 128 with bh1 = 128); 64: register-staged
+    int bk;             // 32: LDS-direct block GEMM (always for bm = 256; optional for bm = 64 / 128 with bh1 = 128); 64: register-staged;
+                        // 128: the streaming kernel (bm = 16 or 32, one row block)
     int bh1;            // hidden slice of a phase-1 item: 128 / 64 / 32 (bm <= 128), 256 or 128 gated (bm = 256)
+    int bn2;            // output columns of a phase-2 item: 256, streaming kernel 64
     int splits, ksplit; // phase-2 ranges of the hidden dimension (splits == 1: no partial planes)
     int raster;         // row blocks per XCD patch
     int gate_split;     // gated chain with its branches on different workgroups (phase-1 items are not gated then)
@@ -53,6 +55,8 @@ int two_phase_max_splits(int64_t M, int64_t N2);
 // Weights far larger than the 256 MB memory-side cache (above 512 MB): the two-phase kernel streams
 // them with the non-temporal hint (row blocks below 256)
 bool weights_streamed(int dtype, int gated, int64_t K, int64_t N1, int64_t N2);
+// the same for the streaming kernel
+bool stream_hint(int dtype, int gated, int64_t K, int64_t N1, int64_t N2);
 bool two_phase_geometry(const ffuse_plan_t& p, int gated, int64_t M, int64_t N1, int64_t N2, TwoPhaseGeometry* out);
 // Which groups of workgroups (blockIdx % 8; the kernel deals its work items group by group) a group has to
 // wait for between the phases: byte g of the result has bit h set when some phase-2 item of group g reads a
