@@ -30,7 +30,7 @@ namespace ffuse {
 // and too large for the memory-side cache to keep; the caller picks the instantiation)
 template <typename T, bool GATED, int BM, int BH, int WM, int WN, bool CONV = false, bool NT = false>
 struct FirstGemm {
-    static_assert(WM * WN == 4, "four waves");
+    static_assert(WM * WN == 4 || WM * WN == 8, "four waves; eight with the loaders that are made for them");
     typedef typename Mma<T>::vec8 vec8;
     static constexpr int G = GATED ? 2 : 1;
     static constexpr int WMR = BM / WM, WHR = BH / WN;  // rows / columns per wave

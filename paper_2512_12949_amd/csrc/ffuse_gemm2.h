@@ -40,19 +40,29 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
     static constexpr int A_RING = NSA * XBW;
     static constexpr int LDS_BYTES = A_RING + NS * BST;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-    // BM = 32: a super-stage is 4 instructions, one per wave, all issued on even steps; odd steps
-    // issue no A load (any NS - 2 consecutive steps still issue the same number of loads per wave)
-    static constexpr bool SMALL_A = BM == 32;
-    static constexpr int XI = SMALL_A ? 1 : BM / 64;   // A load instructions per wave per step
-    static constexpr int QH = SMALL_A ? 0 : BM / 16;   // A instructions per step, whole workgroup
+    // Four waves or eight.  A wave's LDS-direct loads go out one after the other (1 KB per 140 ns and wave from HBM, whatever
+    // the depth of the ring): four waves stream 29 GB/s into a workgroup, eight 46.  And eight waves leave two per SIMD, so
+    // that the matrix cores work through one's barrier and fragment reads on the other's account.
+    static constexpr int NW = WM * WN;
+    // A instructions of a super-stage (8 rows each): XI per wave and step, or one per wave on even steps (SMALL_A)
+    static constexpr int IA = BM / 8;
+    static constexpr bool SMALL_A = IA == NW;
+    static constexpr int XI = SMALL_A ? 1 : IA / (2 * NW);
+    static constexpr int QH = SMALL_A ? 0 : IA / 2;   // A instructions per step, whole workgroup
     static constexpr int ROWB = BH * 2;
     static constexpr int RPI = 1024 / ROWB;
-    static constexpr int BI = 32 / RPI / 4;
-    static constexpr int NLOAD = XI + G * BI;
+    // B instructions of a stage and matrix: BI per wave; or, where there is one for every other wave, the halves of the waves
+    // take a matrix each (gated: HALF_B) or a stage each in turn (ALT_B, by the parity of the step that loads it).
+    static constexpr int IB = 32 / RPI;
+    static constexpr bool HALF_B = IB == NW / 2 && GATED, ALT_B = IB == NW / 2 && !GATED;
+    static constexpr int BI = HALF_B || ALT_B ? 1 : IB / NW;
+    static_assert(BI >= 1 && XI >= 1, "an instruction a wave");
+    static constexpr int NB = HALF_B ? BI : G * BI;    // ... of both matrices
+    static constexpr int NLOAD = XI + NB;
     static constexpr int NM = HT * MT * G;
     static constexpr int NR = MT + HT * G;
     // loads a wave issues in NS - 2 consecutive steps: what may still be in flight at a step's barrier
-    static constexpr int WAITN = SMALL_A ? (NS - 2) * G * BI + (NS - 2) / 2 : (NS - 2) * NLOAD;
+    static constexpr int WAITN = (ALT_B ? (NS - 2) / 2 : (NS - 2) * NB) + (SMALL_A ? (NS - 2) / 2 : (NS - 2) * XI);
     static_assert((NS == 4 || NS == 8) && WAITN <= 63, "ring depth: the vmcnt field holds 6 bits");
 
     struct Ctx {
@@ -67,6 +77,7 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
         uint32_t boff[BI];
         uint32_t abase, brow;
         int KX;
+        int half;               // which half of the waves this one is in
         uint32_t lds_a, lds_b;  // LDS offsets (within a super-stage / a B stage) of this wave's first instruction
         uint32_t rdx[MT], rdw[HT];
     };
@@ -90,9 +101,13 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
     }
     static __device__ __forceinline__ void init_b(Ctx& c, const void* B, const void* B3, uint32_t b_bytes,
                                                   uint32_t ldb, uint32_t ncols, uint32_t n0, int tid) {
-        const int wave = tid >> 6, lane = tid & 63;
+        const int lane = tid & 63;
+        int wave = tid >> 6;
         c.rw[0] = make_rsrc(B, b_bytes);
         if (GATED) c.rw[G - 1] = make_rsrc(B3, b_bytes);
+        if constexpr (HALF_B)
+            if (__builtin_amdgcn_readfirstlane(wave) >= NW / 2) c.rw[0] = c.rw[G - 1];
+        if constexpr (HALF_B || ALT_B) wave &= NW / 2 - 1;
         c.brow = ldb * 2u;
 #pragma unroll
         for (int j = 0; j < BI; ++j) {
@@ -107,8 +122,9 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
         const int wm = wave % WM, wn = wave / WM;
         const uint32_t x = lane & 31, h = lane >> 5;
+        c.half = wave / (NW / 2);
         c.lds_a = (uint32_t)(wave * XI) * 1024u;
-        c.lds_b = (uint32_t)(wave * BI) * 1024u;
+        c.lds_b = (uint32_t)((ALT_B ? wave & (NW / 2 - 1) : wave) * BI) * 1024u;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const uint32_t row = wm * WMR + 32 * mt + x;
@@ -133,6 +149,7 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
 
     // What a step loads: half `par` (0: upper rows, 1: lower rows) of the A super-stage that starts at
     // column kx into super-stage slot `sa`, and the B stage of rows kw.. into stage slot `sb`.
+    // (par is also the parity of the step that loads the B stage)
     struct Load {
         uint32_t sa, sb;   // LDS byte addresses of the A slot / B slot
         int kx, kw, par;
@@ -149,10 +166,11 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
             lds_dma16(c.rx, ok ? xo + half * c.xhalf + c.abase + (uint32_t)l.kx * 2u : kOob,
                       l.sa + c.lds_a + half * (uint32_t)(QH * 1024) + (uint32_t)i * 1024u);
         } else {
+            if (ALT_B && l.par != c.half) return;
             const int which = (i - XI) / BI, j = (i - XI) % BI;
             const uint32_t off = c.boff[j];
             const uint32_t vo = (off == kOob || !l.bvalid) ? kOob : off + (uint32_t)l.kw * c.brow;
-            const uint32_t la = l.sb + c.lds_b + (uint32_t)which * WB + (uint32_t)j * 1024u;
+            const uint32_t la = l.sb + c.lds_b + (uint32_t)which * WB + (uint32_t)j * 1024u;   // (HALF_B: lds_b runs on into the second matrix)
             if (NT_) lds_dma16_nt(c.rw[which], vo, la);
             else lds_dma16(c.rw[which], vo, la);
         }
@@ -230,7 +248,7 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
         const uint32_t b_lds = (uint32_t)(uintptr_t)smem + (uint32_t)A_RING;
 #pragma unroll
         for (int sb = 0; sb < NS - 1; ++sb) {
-            const Load l{0u, b_lds + (uint32_t)(sb * BST), 0, kbegin + 32 * sb, 0, sb < KT};
+            const Load l{0u, b_lds + (uint32_t)(sb * BST), 0, kbegin + 32 * sb, 1 - (sb & 1), sb < KT};
 #pragma unroll
             for (int i = XI; i < NLOAD; ++i) issue_one(c, l, 0, i);
         }
@@ -259,7 +277,7 @@ struct WideGemm : FirstGemm<T, GATED, BM, BH, WM, WN> {
             for (int d = 0; d < 2; ++d) {
                 const int sb = 2 * u + d;
                 if (sb <= NS - 2) {
-                    const Load l{0u, b_lds + (uint32_t)(sb * BST), 0, kbegin + 32 * sb, 0, sb < KT};
+                    const Load l{0u, b_lds + (uint32_t)(sb * BST), 0, kbegin + 32 * sb, 1 - (sb & 1), sb < KT};
 #pragma unroll
                     for (int i = XI; i < NLOAD; ++i) issue_one(c, l, xlim, i);
                 }

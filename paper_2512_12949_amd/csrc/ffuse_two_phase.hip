@@ -40,7 +40,7 @@ namespace ffuse {
 // there are CUs: 128-column slices (four waves along the columns), 64 (2 x 2 waves) or 32
 // (four waves along the rows) give N1/128, N1/64 or N1/32 of them.
 template <typename T, bool GATED, int BM, bool CONV, int BH1_, bool DEEP_> struct TwoPhaseGemms {
-    static constexpr int BH1 = BH1_;
+    static constexpr int BH1 = BH1_, WAVES = 4;
     static constexpr int WM1 = BH1 == 128 ? 1 : (BH1 == 64 ? 2 : 4);
     template <bool NT> using G1 = FirstGemm<T, GATED, BM, BH1, WM1, 4 / WM1, CONV, NT>;   // phase 1: X * W1 (, X * W3); CONV: im2col(X) * W1
     template <bool NT> using G2 = FirstGemm<T, false, BM, 256, 1, 4, false, NT>;   // phase 2: H * W2
@@ -49,7 +49,7 @@ template <typename T, bool GATED, int BM, bool CONV, int BH1_, bool DEEP_> struc
     static constexpr bool PREFETCH = false;
 };
 template <typename T, bool GATED, int BH1_, bool DEEP_> struct TwoPhaseGemms<T, GATED, 256, false, BH1_, DEEP_> {
-    static constexpr int BH1 = GATED ? 128 : 256;
+    static constexpr int BH1 = GATED ? 128 : 256, WAVES = 4;
     template <bool NT> using G1 = DeepGemm<T, GATED, 256, BH1, 2, 2>;
     template <bool NT> using G2 = DeepGemm<T, false, 256, 256, 2, 2>;
     static constexpr bool HAS_NT = false;   // 256-row blocks re-use their weight tiles through L2
@@ -58,11 +58,16 @@ template <typename T, bool GATED, int BH1_, bool DEEP_> struct TwoPhaseGemms<T, 
 };
 // 32 / 64 / 128 rows with the LDS-direct block GEMM and a deeper ring in the first phase: more
 // bytes in flight per workgroup than the register-staged loop can hold, the row operand in
-// whole cache lines
+// whole cache lines.
+// Eight waves where the tile splits into eight (64 x 128 and up, 128 x 64): more loads go out at once and two waves share a
+// SIMD.  Four waves -> eight, us: 400 x 1024 x 2816 gated 30.9 -> 28.6, 800 x 2048 x 8192 76.3 -> 72.2, 1838 x 1536 x 3840
+// 64.4 -> 60.9, 5489 x 1008 x 3872 gated 157.7 -> 147.0, 90 x 4096 x 16384 74.0 -> 70.6, 128 x 4096 x 11008 gated 90.1 -> 88.2.
+// The small tiles keep four: as 4 multiplying + 4 loading waves, 45 x 4096 x 16384 ran in 59.8 instead of 62.1, but
+// 64 x 2048 x 5632 gated in 32.3 instead of 29.6 and 128 x 1024 x 4096 in 22.7 instead of 21.4.
 template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 128, false, 128, true> {
-    static constexpr int BH1 = 128;
-    template <bool NT> using G1 = WideGemm<T, GATED, 128, 128, 2, 2, GATED ? 4 : 8, NT>;
-    template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, 2, 4, NT>;
+    static constexpr int BH1 = 128, WAVES = 8;
+    template <bool NT> using G1 = WideGemm<T, GATED, 128, 128, 2, WAVES / 2, GATED ? 4 : 8, NT>;
+    template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, WAVES / 2, 4, NT>;
     static constexpr bool HAS_NT = true;
     static constexpr bool DEEP = true;
     static constexpr bool PREFETCH = true;
@@ -72,23 +77,23 @@ template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 128, false, 128
 // 64 x 128 wave tiles sustain 0.46.  512 x 4096 x 16384 x 4096: 256 items, one full round instead of two,
 // 163 -> 145 us.  (Gated 128-column slices already are this tile.)
 template <typename T> struct TwoPhaseGemms<T, false, 128, false, 256, true> {
-    static constexpr int BH1 = 256;
-    template <bool NT> using G1 = WideGemm<T, false, 128, 256, 2, 2, 4, NT>;
-    template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, 2, 4, NT>;
+    static constexpr int BH1 = 256, WAVES = 8;
+    template <bool NT> using G1 = WideGemm<T, false, 128, 256, 2, WAVES / 2, 4, NT>;
+    template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, WAVES / 2, 4, NT>;
     static constexpr bool HAS_NT = true;
     static constexpr bool DEEP = true;
     static constexpr bool PREFETCH = true;
 };
 template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 128, false, 64, true> {
-    static constexpr int BH1 = 64;
-    template <bool NT> using G1 = WideGemm<T, GATED, 128, 64, 2, 2, 8, NT>;
-    template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, 2, 4, NT>;
+    static constexpr int BH1 = 64, WAVES = 8;
+    template <bool NT> using G1 = WideGemm<T, GATED, 128, 64, WAVES / 2, 2, 8, NT>;
+    template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, WAVES / 2, 4, NT>;
     static constexpr bool HAS_NT = true;
     static constexpr bool DEEP = true;
     static constexpr bool PREFETCH = true;
 };
 template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 64, false, 64, true> {
-    static constexpr int BH1 = 64;
+    static constexpr int BH1 = 64, WAVES = 4;
     template <bool NT> using G1 = WideGemm<T, GATED, 64, 64, 2, 2, 8, NT>;
     template <bool NT> using G2 = WideGemm<T, false, 64, 256, 2, 2, 4, NT>;
     static constexpr bool HAS_NT = true;
@@ -96,7 +101,7 @@ template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 64, false, 64, 
     static constexpr bool PREFETCH = true;
 };
 template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 32, false, 128, true> {
-    static constexpr int BH1 = 128;
+    static constexpr int BH1 = 128, WAVES = 4;
     template <bool NT> using G1 = WideGemm<T, GATED, 32, 128, 1, 4, 8, NT>;   // (a sixteen-stage ring measured no faster)
     template <bool NT> using G2 = WideGemm<T, false, 32, 256, 1, 4, 8, NT>;
     static constexpr bool HAS_NT = true;
@@ -104,9 +109,9 @@ template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 32, false, 128,
     static constexpr bool PREFETCH = true;
 };
 template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 64, false, 128, true> {
-    static constexpr int BH1 = 128;
-    template <bool NT> using G1 = WideGemm<T, GATED, 64, 128, 2, 2, GATED ? 4 : 8, NT>;
-    template <bool NT> using G2 = WideGemm<T, false, 64, 256, 2, 2, 4, NT>;
+    static constexpr int BH1 = 128, WAVES = 8;
+    template <bool NT> using G1 = WideGemm<T, GATED, 64, 128, 2, WAVES / 2, GATED ? 4 : 8, NT>;
+    template <bool NT> using G2 = WideGemm<T, false, 64, 256, 2, WAVES / 2, 4, NT>;
     static constexpr bool HAS_NT = true;
     static constexpr bool DEEP = true;
     static constexpr bool PREFETCH = true;
@@ -182,7 +187,7 @@ __device__ __forceinline__ void two_phase_join(const TwoPhaseArgs& a, int tid, i
     for (int idx = loc; map_item(MB, 2 * NS, a.raster, xcd, idx, rb, s); idx += GX) {
         if (s & 1) continue;
         s >>= 1;
-        for (int u = tid; u < BM * UPR; u += 256) {
+        for (int u = tid; u < BM * UPR; u += (int)blockDim.x) {
             const int64_t row = (int64_t)rb * BM + u / UPR;
             const int col = s * BH1 + 8 * (u % UPR);
             if (row >= a.M || col >= a.N1) continue;
@@ -275,8 +280,8 @@ __device__ __forceinline__ void two_phase_prefetch(const TwoPhaseArgs& a, char* 
 // a.K = 9 * a.conv_ic); everything after the first product's loads is unchanged.
 // a.nt selects, per launch, the instantiations of the block GEMMs that stream the weights with
 // the non-temporal hint (row blocks below 256 only): the loops themselves stay branch-free.
-template <typename T, bool GATED, int BM, bool CONV = false, int BH1_ = 128, bool DEEP_ = false>
-__global__ __launch_bounds__(256) void fused_two_phase_kernel(TwoPhaseArgs a) {
+template <typename T, bool GATED, int BM, bool CONV, int BH1_, bool DEEP_, int THREADS>
+__global__ __launch_bounds__(THREADS) void fused_two_phase_kernel(TwoPhaseArgs a) {
     typedef TwoPhaseGemms<T, GATED, BM, CONV, BH1_, DEEP_> TG;
     typedef typename TG::template G1<false> G1;
     typedef typename TG::template G2<false> G2;
@@ -397,49 +402,58 @@ hipError_t launch_finalize_planes(int dtype, const float* part, void* Y, int64_t
     return hipGetLastError();
 }
 
-template <typename T, bool GATED> static const void* two_phase_fn(int bm, int bh1, int bk) {
-    if (bk == 32 && bh1 == 128) {   // the LDS-direct block GEMM for small row blocks
-        if (bm == 32) return (const void*)fused_two_phase_kernel<T, GATED, 32, false, 128, true>;
-        if (bm == 64) return (const void*)fused_two_phase_kernel<T, GATED, 64, false, 128, true>;
-        if (bm == 128) return (const void*)fused_two_phase_kernel<T, GATED, 128, false, 128, true>;
-    }
-    if (bk == 32 && bh1 == 64) {
-        if (bm == 64) return (const void*)fused_two_phase_kernel<T, GATED, 64, false, 64, true>;
-        if (bm == 128) return (const void*)fused_two_phase_kernel<T, GATED, 128, false, 64, true>;
-    }
-    if constexpr (!GATED)
-        if (bk == 32 && bm == 128 && bh1 == 256) return (const void*)fused_two_phase_kernel<T, false, 128, false, 256, true>;
-    if (bk == 32 && bm != 256) return nullptr;
-    if (bm == 32 && bh1 == 128) return (const void*)fused_two_phase_kernel<T, GATED, 32>;
-    if (bm == 64 && bh1 == 128) return (const void*)fused_two_phase_kernel<T, GATED, 64>;
-    if (bm == 64 && bh1 == 64) return (const void*)fused_two_phase_kernel<T, GATED, 64, false, 64>;
-    if (bm == 128 && bh1 == 128) return (const void*)fused_two_phase_kernel<T, GATED, 128>;
-    if (bm == 128 && bh1 == 64) return (const void*)fused_two_phase_kernel<T, GATED, 128, false, 64>;
-    if constexpr (!GATED)
-        if (bm == 128 && bh1 == 32) return (const void*)fused_two_phase_kernel<T, GATED, 128, false, 32>;
-    if (bm == 256) return (const void*)fused_two_phase_kernel<T, GATED, 256>;
-    return nullptr;
+struct TwoPhaseFn {
+    const void* fn;
+    int threads;
+};
+template <typename T, bool GATED, int BM, bool CONV = false, int BH1 = 128, bool DEEP = false> static TwoPhaseFn two_phase_kernel() {
+    constexpr int threads = 64 * TwoPhaseGemms<T, GATED, BM, CONV, BH1, DEEP>::WAVES;
+    return {(const void*)fused_two_phase_kernel<T, GATED, BM, CONV, BH1, DEEP, threads>, threads};
 }
 
-template <typename T> static const void* two_phase_conv_fn(int bm, int bh1) {
+template <typename T, bool GATED> static TwoPhaseFn two_phase_fn(int bm, int bh1, int bk) {
+    if (bk == 32 && bh1 == 128) {   // the LDS-direct block GEMM for small row blocks
+        if (bm == 32) return two_phase_kernel<T, GATED, 32, false, 128, true>();
+        if (bm == 64) return two_phase_kernel<T, GATED, 64, false, 128, true>();
+        if (bm == 128) return two_phase_kernel<T, GATED, 128, false, 128, true>();
+    }
+    if (bk == 32 && bh1 == 64) {
+        if (bm == 64) return two_phase_kernel<T, GATED, 64, false, 64, true>();
+        if (bm == 128) return two_phase_kernel<T, GATED, 128, false, 64, true>();
+    }
+    if constexpr (!GATED)
+        if (bk == 32 && bm == 128 && bh1 == 256) return two_phase_kernel<T, false, 128, false, 256, true>();
+    if (bk == 32 && bm != 256) return {nullptr, 0};
+    if (bm == 32 && bh1 == 128) return two_phase_kernel<T, GATED, 32>();
+    if (bm == 64 && bh1 == 128) return two_phase_kernel<T, GATED, 64>();
+    if (bm == 64 && bh1 == 64) return two_phase_kernel<T, GATED, 64, false, 64>();
+    if (bm == 128 && bh1 == 128) return two_phase_kernel<T, GATED, 128>();
+    if (bm == 128 && bh1 == 64) return two_phase_kernel<T, GATED, 128, false, 64>();
+    if constexpr (!GATED)
+        if (bm == 128 && bh1 == 32) return two_phase_kernel<T, GATED, 128, false, 32>();
+    if (bm == 256) return two_phase_kernel<T, GATED, 256>();
+    return {nullptr, 0};
+}
+
+template <typename T> static TwoPhaseFn two_phase_conv_fn(int bm, int bh1) {
     if (bh1 == 128) {
-        if (bm == 32) return (const void*)fused_two_phase_kernel<T, false, 32, true>;
-        if (bm == 64) return (const void*)fused_two_phase_kernel<T, false, 64, true>;
-        if (bm == 128) return (const void*)fused_two_phase_kernel<T, false, 128, true>;
+        if (bm == 32) return two_phase_kernel<T, false, 32, true>();
+        if (bm == 64) return two_phase_kernel<T, false, 64, true>();
+        if (bm == 128) return two_phase_kernel<T, false, 128, true>();
     }
     // narrow slices: the table's deepest layers have 256 / 512 hidden channels, two or four 128-column items
     if (bh1 == 64) {
-        if (bm == 64) return (const void*)fused_two_phase_kernel<T, false, 64, true, 64>;
-        if (bm == 128) return (const void*)fused_two_phase_kernel<T, false, 128, true, 64>;
+        if (bm == 64) return two_phase_kernel<T, false, 64, true, 64>();
+        if (bm == 128) return two_phase_kernel<T, false, 128, true, 64>();
     }
-    if (bh1 == 32 && bm == 128) return (const void*)fused_two_phase_kernel<T, false, 128, true, 32>;
-    return nullptr;
+    if (bh1 == 32 && bm == 128) return two_phase_kernel<T, false, 128, true, 32>();
+    return {nullptr, 0};
 }
 
 hipError_t launch_fused_two_phase(int dtype, const TwoPhaseArgs& a, int bm, int bh1, int bk, int grid, hipStream_t st) {
     const bool g = a.W3 != nullptr && a.U == nullptr;   // (a.U: the branches are separate single-branch items)
     if (a.U && (a.W3 == nullptr || a.phases != 3 || a.conv_ic > 0 || (a.N1 & 63))) return hipErrorInvalidValue;
-    const void* fn;
+    TwoPhaseFn fn;
     if (a.conv_ic > 0) {
         // 3x3 first product: one tap per K step of 64, and the shifted addresses must fit 32 bits
         if (g || bk == 32 || a.conv_ic % 64 || a.K != 9 * a.conv_ic || a.conv_h < 1 || a.conv_w < 1) return hipErrorInvalidValue;
@@ -448,10 +462,10 @@ hipError_t launch_fused_two_phase(int dtype, const TwoPhaseArgs& a, int bm, int 
         fn = dtype == 0 ? (g ? two_phase_fn<__bf16, true>(bm, bh1, bk) : two_phase_fn<__bf16, false>(bm, bh1, bk))
                         : (g ? two_phase_fn<_Float16, true>(bm, bh1, bk) : two_phase_fn<_Float16, false>(bm, bh1, bk));
     }
-    if (!fn || grid < 8 || (grid & 7) || a.raster < 1 || a.splits < 1 || a.phases < 1 || a.phases > 3) return hipErrorInvalidValue;
+    if (!fn.fn || grid < 8 || (grid & 7) || a.raster < 1 || a.splits < 1 || a.phases < 1 || a.phases > 3) return hipErrorInvalidValue;
     TwoPhaseArgs copy = a;
     void* params[] = {&copy};
-    return launch_resident(fn, grid, params, st);
+    return launch_resident(fn.fn, grid, params, st, fn.threads);
 }
 
 }  // namespace ffuse
