@@ -66,7 +66,9 @@ template <typename T, bool GATED, int BH1_, bool DEEP_> struct TwoPhaseGemms<T, 
 // 64 x 2048 x 5632 gated in 32.3 instead of 29.6 and 128 x 1024 x 4096 in 22.7 instead of 21.4.
 template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 128, false, 128, true> {
     static constexpr int BH1 = 128, WAVES = 8;
-    template <bool NT> using G1 = WideGemm<T, GATED, 128, 128, 2, WAVES / 2, GATED ? 4 : 8, NT>;
+    // (4 x 2 waves of 32 x 64, not 2 x 4 of 64 x 32: a wave's rows of the intermediate are then whole cache lines when they are
+    // written through.  Gated 4574 x 896 x 3896 x 896: 136 us as 64 x 32, 127 so; 6181 x 320 x 3960 x 320: 93.5, 88; four waves 133, 95)
+    template <bool NT> using G1 = WideGemm<T, GATED, 128, 128, 4, WAVES / 4, GATED ? 4 : 8, NT>;
     template <bool NT> using G2 = WideGemm<T, false, 128, 256, 2, WAVES / 2, 4, NT>;
     static constexpr bool HAS_NT = true;
     static constexpr bool DEEP = true;
