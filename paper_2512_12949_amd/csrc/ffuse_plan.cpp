@@ -568,8 +568,14 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         const double per_item = (sg.bk == 32 && sg.bm < 256) ? 0.8e-6 : 7.8e-6, per_item2 = 2.56e-6;
         // weights streamed with the non-temporal hint are not kept for the next row block: each streams its own copy
         const double copies = (weights_streamed(dtype, gated, K, N1, N2) && sg.bm < 256) ? mb : 1.0;
-        const double t1 = copies * b1 / std::min(warm * d.hbm_bw, std::min(items1, (double)d.cus) * per_wg1) + re1 / d.fabric_bw + per_item * cdiv(items1, d.cus);
-        const double t2 = copies * b2 / std::min(warm * d.hbm_bw, std::min(items, (double)d.cus) * per_wg2) + re2 / d.fabric_bw + per_item2 * cdiv(items, d.cus);
+        // Items are dealt statically, so that 264 of them stream as long as 512 (gated 38 x 4648 x 16872 x 4648: 264 slices of 64
+        // columns 152 us, 132 of 128 125); and the row blocks that share a weight slice each load it, the repeats at little
+        // more than the stream's own rate: with them free, two 64-row blocks of 143 x 3200 x 7272 x 3200 were predicted in 48 us
+        // for 58.  Exponent fitted on 4000 plans of 315 layers of 33-28000 rows.  (256-row blocks are bound by their products.)
+        const double share = std::pow(std::min(mb, 4.0), 0.84);
+        const auto streams = [&](double n) { return sg.bm == 256 ? std::min(n, (double)d.cus) : n / cdiv(n, d.cus) / share; };
+        const double t1 = copies * b1 / std::min(warm * d.hbm_bw, streams(items1) * per_wg1) + re1 / d.fabric_bw + per_item * cdiv(items1, d.cus);
+        const double t2 = copies * b2 / std::min(warm * d.hbm_bw, streams(items) * per_wg2) + re2 / d.fabric_bw + per_item2 * cdiv(items, d.cus);
         // planes are written and read once; small transfers reach about half the cache rate
         const double planes = sg.splits > 1 ? 2.0 * 4.0 * m * n2 * sg.splits / (0.615 * d.fabric_bw) : 0.0;
         // matrix-core time of each phase: items run one per CU, at the block GEMM's efficiency
@@ -659,9 +665,12 @@ void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1,
         static const int bms[] = {32, 64, 128, 256};
         static const int rasters2[] = {4, 2, 8, 1};   // the model does not tell these apart: measured order of preference
         for (int bm : bms) {
-            // measured: two 64-row blocks beat one of 128 on the m = 128 shapes (half the row-operand
-            // bytes per item, half the planes); more, or smaller, blocks lose
-            if (bm < 128 && M > (bm == 64 ? 128 : bm)) continue;
+            // Up to 256 rows 64-row blocks are tried against 128-row ones (half the row-operand bytes per item, twice the items):
+            // of 110 drawn layers of 65-256 rows the better of both was 5 % faster on average than 128-row blocks above
+            // 128 rows (218 x 896 x 3920 x 896: 27.3 us, 21.5).  Above 128 rows not where the direct kernel takes the layer in
+            // one round of single slices and ties (gated 142 x 1152 x 1664 x 1152: 22.5 us, 21.9).  Smaller blocks lose.
+            if (bm < 128 && M > (bm == 64 ? 256 : bm)) continue;
+            if (bm == 64 && M > 128 && N1 <= 2048 && N2 <= 2048 && cdiv((double)M, 16.0) * cdiv((double)N1, 64.0) <= kDevice.cus) continue;
             if (bm > 32 && M <= bm / 2) continue;             // more than half a block of padding
             // 128 / 64 / 32: register-staged loop with that slice width; -128 / -64 / -256: LDS-direct loop
             static const int slices[] = {128, 64, 32, -128, -64, -256};
