@@ -254,7 +254,9 @@ bool fused_reduce_tile_ok(int gated, int bm, int bh) {
 
 // Fraction of the MFMA peak a block GEMM sustains on a compute-bound problem, by tile shape
 // (measured on the two-phase kernel's first phase, 4096 x 4096 x 16384 and 2048 x 4096 x
-// 2 * 11008).  Four waves share a rows x cols tile 2 x 2; per MFMA a wave reads
+// 2 * 11008, with four waves.  Eight do 3-20 % better on the smaller tiles in calls below 100 us and about the same in
+// longer ones, at the power limit: priced higher, 128-row plans displaced 256-row ones that are 5-20 % faster there, so the
+// figures stay).  Four waves share a rows x cols tile 2 x 2; per MFMA a wave reads
 // r ~ 1 / wave rows + 1 / wave cols operand fragments from LDS, and the smaller the tile the
 // more of the loop is LDS reads rather than matrix instructions.  The 256 x 256 tile runs at
 // the chip's power limit; smaller tiles run at a higher clock but stay LDS-bound.
