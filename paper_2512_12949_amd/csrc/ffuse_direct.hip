@@ -159,7 +159,12 @@ __global__ __launch_bounds__(64 * NW) void fused_direct_kernel(DirectArgs a) {
             for (int u = 0; u < DEPTH; ++u) {
                 multiply(slot[u], ksteps - DEPTH + u);
                 __builtin_amdgcn_sched_barrier(0);
-                load(slot[u], ch + 1, u);
+                // Loads of a slice that is not there are branched over: range-checked zeros cost their issue slots (ranges of two
+                // slices, averages of 8 shapes each: gated, 16 rows, K of 129-256 9.8 -> 9.2 us; 32 rows, K above 256 14.1 -> 13.5;
+                // ungated, 16 rows, K of 65-256 on more than 256 workgroups 4 %).  Not on 16 rows with ungated long K: the last
+                // turn has a form of its own above.  (readfirstlane: a condition that the compiler can fold into the loop's own
+                // takes 130 registers in the 32-row short form, which has 128 for two workgroups a CU.)
+                if ((!GATED && !SHORT && R == 1) || __builtin_amdgcn_readfirstlane(ch_end - ch) > 1) load(slot[u], ch + 1, u);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
