@@ -402,7 +402,7 @@ int run_plan(const ffuse_plan_t& plan, int dtype, const void* X, const void* W1,
                             dg.ranges, dg.slices, conv.ic, conv.h, conv.w};
         g.exch_err = nullptr;
         Timer t(st);
-        if (ffuse::launch_fused_direct(dtype, d, dg.bm, dg.ng, st) != hipSuccess) return FFUSE_ERR_LAUNCH;
+        if (ffuse::launch_fused_direct(dtype, d, dg.bm, dg.ng, g.cus, st) != hipSuccess) return FFUSE_ERR_LAUNCH;
         t.stop();
         g.last_plan = plan;
         return FFUSE_OK;

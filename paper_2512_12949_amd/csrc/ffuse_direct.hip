@@ -17,9 +17,10 @@
 // K alone; the 128-row reduce tiles walk K in LDS stages with a barrier each.  Here a slice costs two barriers and
 // about K / 512 round trips.  Against that, operands are re-read from L2 by every row block.  Eight waves rather than
 // four issue the loads and multiplies of a slice: most of these problems have one workgroup a CU or less, and the walk
-// is bound by how fast its waves issue.  Four -> eight: 3136 x 64 x 256 x 64 7.0 -> 5.7 us, 128 x 384 x 1536 x 384 10.8 ->
+// is bound by how fast its waves issue.  (Which forms keep four: direct_waves.)  Four -> eight: 3136 x 64 x 256 x 64 7.0 -> 5.7 us, 128 x 384 x 1536 x 384 10.8 ->
 // 10.2, 3x3 chains 196 x 2304 x 256 x 1024 15.7 -> 14.8, 49 x 4608 x 512 x 2048 25.5 -> 23.3; 140 drawn shapes of up to 4 Gflop
 // 3 % on average, those of this kernel 6.  (A ring of three or four steps a wave, with more of K padded: 0-20 % slower.)
+// Outputs above 1024 columns with ranges of several slices spill 1-4 registers (78-80 with four waves, and 5-9 % slower).
 //
 // Measured (us, the best of the other plans -> this): 3x3 chains 196 pixels x 2304 x 256 x 1024 41 -> 15, 49 x 4608 x
 // 512 x 2048 47 -> 23, 6272 x 576 x 64 x 256 21 -> 8; 128 x 384 x 1536 x 384 17.4 -> 10.2; 3136 x 64 x 256 x 64
@@ -274,55 +275,61 @@ __global__ __launch_bounds__(64 * NW) void fused_direct_kernel(DirectArgs a) {
             }
 }
 
-// Eight waves, but four for the gated chain beyond K = 256, whose eight spill: 30 x 768 x 2048 x 768 13.6 us with four, 15.0
-// with eight, 142 x 1152 x 1664 x 1152 23.0 and 23.2.
-template <bool GATED> static constexpr int direct_waves(bool short_k) { return GATED && !short_k ? 4 : 8; }
-
 // NC: 256-column blocks of the output
-template <typename T, bool GATED, bool CONV, int R, int NC, bool SHORT, bool MORE> static const void* direct_variant() {
-    constexpr int NW = direct_waves<GATED>(SHORT), DEPTH = SHORT ? 1 : 2;
+template <typename T, bool GATED, bool CONV, int R, int NC, bool SHORT, bool MORE, int NW> static const void* direct_variant() {
+    constexpr int DEPTH = SHORT ? 8 / NW : 2;
     if constexpr (NW == 4) return (const void*)fused_direct_kernel<T, GATED, CONV, R, NC, 1, SHORT, MORE, DEPTH, 4>;
     else if constexpr (NC == 1) return (const void*)fused_direct_kernel<T, GATED, CONV, R, 1, 2, SHORT, MORE, DEPTH, 8>;
     else return (const void*)fused_direct_kernel<T, GATED, CONV, R, NC / 2, 1, SHORT, MORE, DEPTH, 8>;
 }
 
-template <typename T, bool GATED, bool CONV, bool MORE> static const void* direct_fn(int bm, int ng, bool short_k) {
+template <typename T, bool GATED, bool CONV, bool MORE> static const void* direct_fn(int bm, int ng, bool short_k, int waves) {
     if constexpr (!CONV) {
         if (short_k) {
-            if (bm == 16) return ng == 1 ? direct_variant<T, GATED, false, 1, 1, true, MORE>() : direct_variant<T, GATED, false, 1, 2, true, MORE>();
-            if (bm == 32) return ng == 1 ? direct_variant<T, GATED, false, 2, 1, true, MORE>() : direct_variant<T, GATED, false, 2, 2, true, MORE>();
+            if constexpr (!GATED && !MORE)
+                if (waves == 4) return bm == 16 && ng == 1 ? direct_variant<T, false, false, 1, 1, true, false, 4>() : nullptr;
+            if (waves != 8) return nullptr;
+            if (bm == 16) return ng == 1 ? direct_variant<T, GATED, false, 1, 1, true, MORE, 8>() : direct_variant<T, GATED, false, 1, 2, true, MORE, 8>();
+            if (bm == 32) return ng == 1 ? direct_variant<T, GATED, false, 2, 1, true, MORE, 8>() : direct_variant<T, GATED, false, 2, 2, true, MORE, 8>();
             return nullptr;
         }
     }
+    constexpr int NW = GATED ? 4 : 8;
+    if (waves != NW) return nullptr;
     if (bm == 16) {
-        if (ng == 1) return direct_variant<T, GATED, CONV, 1, 1, false, MORE>();
-        if (ng == 2) return direct_variant<T, GATED, CONV, 1, 2, false, MORE>();
-        if (ng == 4) return direct_variant<T, GATED, CONV, 1, 4, false, MORE>();
-        if (ng == 8) return direct_variant<T, GATED, CONV, 1, 8, false, MORE>();
+        if (ng == 1) return direct_variant<T, GATED, CONV, 1, 1, false, MORE, NW>();
+        if (ng == 2) return direct_variant<T, GATED, CONV, 1, 2, false, MORE, NW>();
+        if (ng == 4) return direct_variant<T, GATED, CONV, 1, 4, false, MORE, NW>();
+        if (ng == 8) return direct_variant<T, GATED, CONV, 1, 8, false, MORE, NW>();
     }
     if (bm == 32) {
-        if (ng == 1) return direct_variant<T, GATED, CONV, 2, 1, false, MORE>();
-        if (ng == 2) return direct_variant<T, GATED, CONV, 2, 2, false, MORE>();
+        if (ng == 1) return direct_variant<T, GATED, CONV, 2, 1, false, MORE, NW>();
+        if (ng == 2) return direct_variant<T, GATED, CONV, 2, 2, false, MORE, NW>();
     }
     return nullptr;
 }
 
-template <typename T> static const void* direct_fn(bool gated, bool conv, bool more, int bm, int ng, bool short_k) {
-    if (conv) return more ? direct_fn<T, false, true, true>(bm, ng, false) : direct_fn<T, false, true, false>(bm, ng, false);
-    if (gated) return more ? direct_fn<T, true, false, true>(bm, ng, short_k) : direct_fn<T, true, false, false>(bm, ng, short_k);
-    return more ? direct_fn<T, false, false, true>(bm, ng, short_k) : direct_fn<T, false, false, false>(bm, ng, short_k);
+template <typename T> static const void* direct_fn(bool gated, bool conv, bool more, int bm, int ng, bool short_k, int waves) {
+    if (conv) return more ? direct_fn<T, false, true, true>(bm, ng, false, waves) : direct_fn<T, false, true, false>(bm, ng, false, waves);
+    if (gated) return more ? direct_fn<T, true, false, true>(bm, ng, short_k, waves) : direct_fn<T, true, false, false>(bm, ng, short_k, waves);
+    return more ? direct_fn<T, false, false, true>(bm, ng, short_k, waves) : direct_fn<T, false, false, false>(bm, ng, short_k, waves);
 }
 
-hipError_t launch_fused_direct(int dtype, const DirectArgs& a, int bm, int ng, hipStream_t st) {
+hipError_t launch_fused_direct(int dtype, const DirectArgs& a, int bm, int ng, int cus, hipStream_t st) {
     const bool g = a.W3 != nullptr, conv = a.conv_ic > 0;
     if (conv && (g || a.conv_ic % 32 || a.K != 9 * a.conv_ic || a.conv_h < 1 || a.conv_w < 1)) return hipErrorInvalidValue;
     if (a.ranges < 1 || a.slices < 1 || (int64_t)a.ranges * a.slices * 64 < a.N1 || (int64_t)(a.ranges - 1) * a.slices * 64 >= a.N1 ||
         a.N2 > 256 * ng || (a.ranges > 1 && !a.part)) return hipErrorInvalidValue;
     const bool short_k = !conv && a.K <= 256 && ng <= 2;
-    const int waves = g ? direct_waves<true>(short_k) : direct_waves<false>(short_k);
-    const void* fn;
-    fn = dtype == 0 ? direct_fn<__bf16>(g, conv, a.slices > 1, bm, ng, short_k) : direct_fn<_Float16>(g, conv, a.slices > 1, bm, ng, short_k);
     const int64_t grid = (a.M + bm - 1) / bm * a.ranges;
+    const bool shared = grid > cus;
+    const int waves = direct_waves(g, short_k, bm, ng, a.slices, shared);
+    // Where workgroups share a CU, the form for several slices with one slice too: it keeps less across the exchange, 128
+    // registers instead of 132 (32 rows) and 124 instead of 138 (gated, 16 rows), and two workgroups of eight waves on a CU may
+    // have 128 each.  us, averages of 8 shapes on 257-512 workgroups: 32 rows, K of 65-128 12.0 -> 10.6, above 16.4 -> 15.0; gated 13.8 ->
+    // 12.7.
+    const bool more = a.slices > 1 || (shared && short_k && ng == 1 && bm == (g ? 16 : 32));
+    const void* fn = dtype == 0 ? direct_fn<__bf16>(g, conv, more, bm, ng, short_k, waves) : direct_fn<_Float16>(g, conv, more, bm, ng, short_k, waves);
     if (!fn || grid > 0x7fffffff) return hipErrorInvalidValue;
     DirectArgs copy = a;
     void* params[] = {&copy};

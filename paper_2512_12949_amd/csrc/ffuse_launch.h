@@ -124,8 +124,19 @@ hipError_t launch_fused_two_phase(int dtype, const TwoPhaseArgs& a, int bm, int 
 // the streaming kernel: bm = 16 or 32 rows, items of 64 columns in both phases
 hipError_t launch_fused_stream(int dtype, const TwoPhaseArgs& a, int bm, int grid, hipStream_t st);
 hipError_t launch_finalize_planes(int dtype, const float* part, void* Y, int64_t count, int planes, hipStream_t st);
-// bm: rows per workgroup (16 or 32); ng: blocks of 256 output columns (1, 2, and with 16 rows 4 and 8); sums the planes too
-hipError_t launch_fused_direct(int dtype, const DirectArgs& a, int bm, int ng, hipStream_t st);
+// Waves of a workgroup of the small row blocks' kernel.  short_k: K <= 256 and ng <= 2, not a 3x3 chain; shared: more workgroups
+// than compute units.  Eight, but four for the gated chain beyond K = 256, whose eight spill (30 x 768 x 2048 x 768 13.6 us with
+// four, 15.0 with eight, 142 x 1152 x 1664 x 1152 23.0 and 23.2), and on 16 rows with ranges of one slice where workgroups share a
+// CU: three of four waves fit one (162 registers), two of eight, and there is no chain of slices to shorten.  us, eight -> four:
+// K <= 64 on 257-512 workgroups 6.7 -> 6.5, on more 8.7 -> 7.3, K of 65-128 7.8 -> 7.7 and 11.7 -> 10.8, above 9.8 -> 9.9 and 15.3 -> 14.5.
+inline int direct_waves(bool gated, bool short_k, int bm, int ng, int slices, bool shared) {
+    if (gated) return short_k ? 8 : 4;
+    return short_k && shared && bm == 16 && ng == 1 && slices == 1 ? 4 : 8;
+}
+
+// bm: rows per workgroup (16 or 32); ng: blocks of 256 output columns (1, 2, and with 16 rows 4 and 8); cus: compute units;
+// sums the planes too
+hipError_t launch_fused_direct(int dtype, const DirectArgs& a, int bm, int ng, int cus, hipStream_t st);
 hipError_t launch_fused_exchange(int dtype, const ExchangeArgs& a, int wgs_per_group, hipStream_t st);
 hipError_t launch_fused_reduce(int dtype, const FusedArgs& a, int bm, int bh, hipStream_t st);
 hipError_t launch_finalize(int dtype, float* sums, void* Y, int64_t count, hipStream_t st);
