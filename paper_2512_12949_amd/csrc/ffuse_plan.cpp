@@ -211,9 +211,8 @@ bool two_phase_item(int MB, int S, int raster, int grp, int idx, int* i, int* s)
     *s = rem / rows;
     return true;
 }
-}  // namespace
 
-uint64_t two_phase_wait_masks(const TwoPhaseGeometry& g, int64_t M, int64_t N1, int64_t N2) {
+uint64_t enumerate_wait_masks(const TwoPhaseGeometry& g, int64_t M, int64_t N1, int64_t N2) {
     const int MB = (int)((M + g.bm - 1) / g.bm);
     const int NS1 = (int)((N1 + g.bh1 - 1) / g.bh1);
     const int NCB = (int)((N2 + g.bn2 - 1) / g.bn2);
@@ -241,6 +240,26 @@ uint64_t two_phase_wait_masks(const TwoPhaseGeometry& g, int64_t M, int64_t N1, 
         masks |= m << (8 * grp);
     }
     return masks;
+}
+}  // namespace
+
+// Thousands of items at the large shapes: remembered for the last few (geometry, shape) pairs, so that a serving loop pays
+// for them once.  The key is all that the enumeration reads.
+uint64_t two_phase_wait_masks(const TwoPhaseGeometry& g, int64_t M, int64_t N1, int64_t N2) {
+    struct Entry { int64_t key[10]; uint64_t masks; bool used; };
+    static std::mutex mu;
+    static Entry cache[8] = {};
+    static int next = 0;
+    const int64_t key[10] = {g.bm, g.bh1, g.bn2, g.splits, g.ksplit, g.raster, g.gate_split, M, N1, N2};
+    std::lock_guard<std::mutex> lock(mu);
+    for (const Entry& e : cache)
+        if (e.used && std::memcmp(e.key, key, sizeof(key)) == 0) return e.masks;
+    Entry& e = cache[next];
+    next = (next + 1) % 8;
+    std::memcpy(e.key, key, sizeof(key));
+    e.masks = enumerate_wait_masks(g, M, N1, N2);
+    e.used = true;
+    return e.masks;
 }
 
 bool two_phase_groups_independent(const TwoPhaseGeometry& g, int64_t M, int64_t N1, int64_t N2) {

@@ -61,6 +61,7 @@ bool two_phase_geometry(const ffuse_plan_t& p, int gated, int64_t M, int64_t N1,
 // Which groups of workgroups (blockIdx % 8; the kernel deals its work items group by group) a group has to
 // wait for between the phases: byte g of the result has bit h set when some phase-2 item of group g reads a
 // tile of H that a phase-1 item of group h writes.  All ones when the item counts are too large to enumerate.
+// (Remembered for the last few geometries and shapes.)
 uint64_t two_phase_wait_masks(const TwoPhaseGeometry& g, int64_t M, int64_t N1, int64_t N2);
 // every group waits for itself alone
 bool two_phase_groups_independent(const TwoPhaseGeometry& g, int64_t M, int64_t N1, int64_t N2);

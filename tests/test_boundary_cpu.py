@@ -271,3 +271,38 @@ def test_group_local_barrier_condition_matches_the_item_maps():
     assert not ff.ffuse_plan_group_local(ff.make_plan(ff.FAMILY_TWOPHASE, bm=256, bh=256, bn2=256, bk=32, splits=1, raster=4), ff.DT_BF16, False, 4096, 4096, 16384, 4096)
     assert ff.ffuse_plan_group_local(ff.make_plan(ff.FAMILY_TWOPHASE, bm=256, bh=256, bn2=256, bk=32, splits=1, raster=2), ff.DT_BF16, False, 4096, 4096, 16384, 4096)
 
+
+
+def test_remembered_barrier_conditions_are_those_of_their_own_plan():
+    """The condition is remembered for the last plans and shapes that were asked for: plans that differ in one field alone
+    -- rows, slice, ranges, patch, branches apart, the streaming kernel's narrower output items -- or in one size keep theirs
+    in any order, the first time and when remembered."""
+    tp = lambda bm, bh, splits, raster=1, bk=32, gate_split=0, bn2=256: ff.make_plan(
+        ff.FAMILY_TWOPHASE, bm=bm, bh=bh, bn2=bn2, bk=bk, splits=splits, raster=raster, gate_split=gate_split)
+    # (the shape's rows, the plan, gated, the condition: worked out from the item maps by hand or by the tests above)
+    asked = [(16, tp(16, 64, 8, bk=128, bn2=64), False, True), (16, tp(16, 64, 1, bk=128, bn2=64), False, False),
+             (128, tp(128, 64, 8), True, True), (128, tp(128, 64, 8, gate_split=1), True, False), (128, tp(128, 64, 8, raster=1), True, True),
+             (128, tp(128, 64, 2), True, False), (128, tp(128, 128, 8, gate_split=1), True, False), (128, tp(128, 128, 8), True, True),
+             (32, tp(32, 128, 8), False, True), (32, tp(32, 128, 4), False, False)]
+    orders = [asked, asked[::-1], asked + asked, [a for a in asked for _ in range(2)]]
+    for order in orders:
+        for M, plan, gated, want in order:
+            got = ff.ffuse_plan_group_local(plan, ff.DT_BF16, gated, M, 1024, 4096, 4096)
+            assert bool(got) == want, (M, plan.as_dict(), gated, got)
+    # the same plan on shapes that differ in one size, against the item maps of one row block (MB = 1, raster = 1)
+    def independent(bh, bn2, splits, N1, N2):
+        ksplit = (-(-N1 // splits) + 63) // 64 * 64
+        ranges, ns, ncb = -(-N1 // ksplit), -(-N1 // bh), -(-N2 // bn2)
+        per1, per2 = -(-ns // 8), -(-(ncb * ranges) // 8)
+        return all(s // per1 == v // per2 for v in range(ncb * ranges)
+                   for s in range(v // ncb * ksplit // bh, -(-min(N1, (v // ncb + 1) * ksplit) // bh)))
+    shapes = [(4096, 4096), (4096, 4104), (4096, 2048), (4032, 4096), (1000, 4096), (4096, 520), (4096, 4096)]
+    seen = set()
+    for order in (shapes, shapes[::-1]):
+        for N1, N2 in order:
+            want = independent(64, 256, 5, N1, N2)
+            assert bool(ff.ffuse_plan_group_local(tp(128, 64, 5), ff.DT_BF16, True, 128, 1024, N1, N2)) == want, (N1, N2)
+            want8 = independent(64, 256, 8, N1, N2)
+            assert bool(ff.ffuse_plan_group_local(tp(128, 64, 8), ff.DT_BF16, True, 128, 1024, N1, N2)) == want8, (N1, N2)
+            seen |= {want, want8}
+    assert seen == {True, False}
