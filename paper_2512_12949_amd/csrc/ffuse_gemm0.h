@@ -30,7 +30,9 @@ namespace ffuse {
 // and too large for the memory-side cache to keep; the caller picks the instantiation)
 template <typename T, bool GATED, int BM, int BH, int WM, int WN, bool CONV = false, bool NT = false>
 struct FirstGemm {
-    static_assert(WM * WN == 4 || WM * WN == 8, "four waves; eight with the loaders that are made for them");
+    static_assert(WM * WN == 4 || WM * WN == 8, "four waves; eight for what a class with loaders of its own inherits");
+    // this class's own loaders deal a stage to 256 threads
+    static constexpr bool OWN_LOADERS = WM * WN == 4;
     typedef typename Mma<T>::vec8 vec8;
     static constexpr int G = GATED ? 2 : 1;
     static constexpr int WMR = BM / WM, WHR = BH / WN;  // rows / columns per wave
@@ -72,6 +74,7 @@ struct FirstGemm {
     // end of the buffer read as zero.
     static __device__ __forceinline__ void init_a(Ctx& c, const void* A, uint32_t a_bytes, uint32_t base_bytes,
                                                   uint32_t row0, uint32_t lda, int kx, int tid) {
+        static_assert(OWN_LOADERS, "FirstGemm's loaders are for four waves");
         c.rx = make_rsrc(A, a_bytes);
         c.KX = kx;
         c.abase = base_bytes;
@@ -86,6 +89,7 @@ struct FirstGemm {
     // kernel; rows are pixels, K = 9 * IC.
     static __device__ __forceinline__ void init_a_conv(Ctx& c, const void* X, uint32_t x_bytes, uint32_t row0, int64_t npix,
                                                        int H, int W, int IC, int tid) {
+        static_assert(OWN_LOADERS, "FirstGemm's loaders are for four waves");
         c.rx = make_rsrc(X, x_bytes);
         c.KX = 9 * IC;
         c.abase = 0u;
@@ -135,6 +139,7 @@ struct FirstGemm {
     // B operands: [K][ldb] matrices, first column n0 (columns at or past ncols read as zero).
     static __device__ __forceinline__ void init_b(Ctx& c, const void* B, const void* B3, uint32_t b_bytes,
                                                   uint32_t ldb, uint32_t ncols, uint32_t n0, int tid) {
+        static_assert(OWN_LOADERS, "FirstGemm's loaders are for four waves");
         c.wrow = ldb * 2u;
 #pragma unroll
         for (int q = 0; q < WPT; ++q) {
@@ -355,6 +360,7 @@ struct FirstGemm {
     static __device__ __forceinline__ void run(char* smem, const Ctx& c, int kbegin, int kend, f32x16 (&acc)[HT][MT],
                                                f32x16 (&acc3)[GATED ? HT : 1][GATED ? MT : 1], int tid,
                                                uint64_t* t_loop = nullptr) {
+        static_assert(OWN_LOADERS, "FirstGemm's loaders are for four waves");
         zero(acc, acc3);
         const int KT = (kend - kbegin + 63) / 64;
         Stage st;
@@ -378,6 +384,7 @@ struct FirstGemm {
     // flight per CU.  For the bandwidth-bound small-M kernels, whose accumulators are small.
     static __device__ __forceinline__ void run_deep(char* smem, const Ctx& c, int kbegin, int kend, f32x16 (&acc)[HT][MT],
                                                     f32x16 (&acc3)[GATED ? HT : 1][GATED ? MT : 1], int tid) {
+        static_assert(OWN_LOADERS, "FirstGemm's loaders are for four waves");
         zero(acc, acc3);
         const int KT = (kend - kbegin + 63) / 64;
         Stage sa, sb;
