@@ -11,6 +11,7 @@
 // XCD, 32 CUs) -> Infinity Cache (256 MB) -> HBM.  Cross-workgroup sums go through fp32
 // atomics that execute in L2.
 #include "ffuse_plan.h"
+#include "ffuse_launch.h"
 
 #include <algorithm>
 #include <cmath>
@@ -356,8 +357,9 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->fabric_bytes = std::min(8.0, mb) * weights + e * m * k * std::min(8, dg.ranges) + e * m * n2 + planes;
         t->reduce_bytes = planes;
         t->hbm_bytes = t->q_min;
-        t->lds_used = (gated ? 8.0 : 4.0) * dg.bm * 256.0 + dg.bm * 144.0;
-        t->acc_regs = (double)dg.ng * dg.bm;
+        const int waves = direct_waves(gated, shortk, dg.bm, dg.ng, dg.slices, wgs > d.cus);
+        t->lds_used = g * waves * dg.bm * 256.0 + dg.bm * 144.0;            // a partial tile a wave and branch, and H
+        t->acc_regs = (double)dg.bm * (waves == 4 ? dg.ng : std::max(1, dg.ng / 2));   // (eight waves on one column block: half the hidden columns each)
         t->feasible = t->lds_used <= d.lds_bytes && t->acc_regs <= d.acc_regs;
         t->t_hbm = t->hbm_bytes / d.hbm_bw;
         t->t_fabric = t->fabric_bytes / d.fabric_bw;

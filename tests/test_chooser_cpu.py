@@ -352,13 +352,31 @@ def test_the_models_choice_against_measured_plans():
 
 
 def test_accumulators_of_the_small_row_blocks():
-    """bm rows x 256 ng output columns of fp32 over 256 lanes: bm ng registers per lane, within the device's 256."""
+    """bm rows x 256 ng output columns of fp32 over the 512 lanes of eight waves (over 256 of them where ng = 1: the others
+    hold the other half of the hidden columns), over 256 lanes with four waves: gated with K above 256."""
     for N2, ng in ((8, 1), (256, 1), (264, 2), (512, 2), (1000, 4), (2048, 8)):
         for bm in (16, 32):
             if bm == 32 and N2 > 512:
                 continue
-            t = ff.ffuse_traffic_model(ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=2), ff.DT_BF16, False, 100, 512, 512, N2)
+            plan = ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=2)
+            t = ff.ffuse_traffic_model(plan, ff.DT_BF16, False, 100, 512, 512, N2)
+            assert t.feasible and t.acc_regs == bm * max(1, ng // 2), (N2, bm, t.acc_regs)
+            t = ff.ffuse_traffic_model(plan, ff.DT_BF16, True, 100, 512, 512, N2)
             assert t.feasible and t.acc_regs == bm * ng <= 256, (N2, bm, t.acc_regs)
+
+
+def test_lds_of_the_small_row_blocks():
+    """The model's LDS bytes are the kernels': the figures of the compiler's resource report (-Rpass-analysis=kernel-resource-usage)."""
+    # (rows, K, N1, N2, bm, ranges, gated): K up to 256 and past it, one slice a range and several, fewer and more workgroups than
+    # the 256 compute units
+    for M, K, N1, N2, bm, splits, gated, lds in (
+            (100, 512, 512, 256, 16, 2, False, 35072), (100, 256, 512, 256, 16, 2, False, 35072), (100, 512, 512, 256, 32, 2, False, 70144),
+            (100, 256, 512, 512, 32, 2, False, 70144), (100, 512, 512, 256, 16, 2, True, 35072), (100, 512, 512, 256, 32, 2, True, 70144),
+            (100, 256, 512, 256, 16, 2, True, 67840), (100, 256, 512, 512, 32, 2, True, 135680), (100, 264, 512, 256, 16, 8, False, 35072),
+            (4096, 64, 64, 64, 16, 1, False, 35072), (4097, 64, 64, 64, 16, 1, False, 18688), (4097, 64, 128, 64, 16, 1, False, 35072),
+            (4097, 64, 64, 264, 16, 1, False, 35072), (8200, 64, 64, 64, 32, 1, False, 70144), (4097, 64, 64, 64, 16, 1, True, 67840)):
+        t = ff.ffuse_traffic_model(ff.make_plan(ff.FAMILY_REDUCE, bm=bm, bh=64, bk=32, splits=splits), ff.DT_BF16, gated, M, K, N1, N2)
+        assert t.feasible and t.lds_used == lds, (M, K, N1, N2, bm, splits, gated, t.lds_used)
 
 
 def test_fp32_predictions_against_measured_calls():
