@@ -336,21 +336,24 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
     t->feasible = 1;
 
     if (is_direct(p)) {
-        // Fitted with the two-phase constants below (see there): the measured calls of plans worth running scatter by 8 %
-        // round it.  A slice of 64 hidden columns costs two barriers and the issue of its loads: up to K = 256
-        // 1.05 us + 3.7 ns per k (gated 1.3 of that); beyond, 1.43 us per turn of the operand ring (512 k, gated 256: 1.55)
-        // and 0.56 per block of 256 output columns.  32 rows take 1.42 times as long as 16.  Workgroups run one per CU;
-        // two of the smallest variant share one and then take 0.9 of twice the time.  Planes: their bytes, a second
-        // launch, eight at a time.
+        // A slice of 64 hidden columns costs two barriers and the issue of its loads: up to K = 256 0.72 us + 3.0 ns per k and
+        // 0.27 for a second block of 256 output columns (gated 1.45 of that; 32 rows 1.56); beyond, 1.21 us per turn of the
+        // operand ring (512 k, gated 256: 1.26) and 0.52 per block of output columns (32 rows 1.31).  Workgroups run one per CU;
+        // two of the smallest variant share one and then take 0.8 of twice the time.  Planes: their bytes, a second launch,
+        // eight at a time.  Fitted on 2940 timings of 1300 shapes with the present waves (eight; four where gated beyond K =
+        // 256): no bias in any variant beyond 5 %, 7 % scatter.  (The constants of the four-wave kernel predicted these calls 8 %
+        // high on average, the smallest variant 14, and layers went to two-phase plans: 96 x 1152 x 1920 x 1152 21.6 us there,
+        // 17.3 here.)  The planes' bytes are no part of the walk's time: counted in it, they hid what 16 rows save over 32
+        // (gated 142 x 512 x 1536 x 512, 24 ranges: 15.4 us on 32 rows, 13.4 on 16).
         DirectGeometry dg;
         t->feasible = direct_geometry(p, M, N1, N2, &dg) ? 1 : 0;
         if (!t->feasible) return;
-        const double mb = cdiv(m, dg.bm), wgs = mb * dg.ranges, big = dg.bm == 32 ? 1.42 : 1.0;
-        const bool shortk = K <= 256 && dg.ng <= 2;
-        const double slice = 1e-6 * big * (shortk ? (1.05 + 0.00368 * k) * (gated ? 1.3 : 1.0)
-                                                  : 0.198 + (gated ? 1.55 * cdiv(k, 256.0) : 1.43 * cdiv(k, 512.0)) + 0.556 * dg.ng);
+        const double mb = cdiv(m, dg.bm), wgs = mb * dg.ranges;
+        const bool shortk = K <= 256 && dg.ng <= 2, tall = dg.bm == 32;
+        const double slice = 1e-6 * (shortk ? (0.717 + 0.003 * k + 0.268 * (dg.ng - 1)) * (gated ? 1.446 : 1.0) * (tall ? 1.562 : 1.0)
+                                            : (0.367 + (gated ? 1.262 * cdiv(k, 256.0) : 1.214 * cdiv(k, 512.0)) + 0.522 * dg.ng) * (tall ? 1.307 : 1.0));
         double rounds = cdiv(wgs, d.cus);
-        if (shortk && dg.ng == 1 && rounds > 1.0) rounds *= 0.9;
+        if (shortk && dg.ng == 1 && rounds > 1.0) rounds *= 0.8;
         const double weights = e * (g * k * n1 + n1 * n2), planes = dg.ranges > 1 ? 2.0 * 4.0 * m * n2 * dg.ranges : 0.0;
         t->workgroups = (int)std::min(wgs, (double)d.cus);
         t->l2_bytes = mb * weights + e * m * k * dg.ranges;
@@ -365,8 +368,8 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->t_fabric = t->fabric_bytes / d.fabric_bw;
         t->t_l2 = t->l2_bytes / d.l2_bw;
         t->t_mfma = rounds * dg.slices * slice;
-        t->t_reduce = dg.ranges > 1 ? planes / (0.492 * d.fabric_bw) + 1.56e-6 + 0.421e-6 * cdiv(dg.ranges, 8.0) : 0.0;
-        t->t_pred = 2.49e-6 + std::max({t->t_mfma, t->t_hbm, t->t_fabric}) + t->t_reduce;
+        t->t_reduce = dg.ranges > 1 ? planes / (0.413 * d.fabric_bw) + 1.46e-6 + 0.501e-6 * cdiv(dg.ranges, 8.0) : 0.0;
+        t->t_pred = 2.39e-6 + std::max({t->t_mfma, t->t_hbm, (t->fabric_bytes - planes) / d.fabric_bw}) + t->t_reduce;
         return;
     }
     if (p.family == FFUSE_FAMILY_REDUCE) {

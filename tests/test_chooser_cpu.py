@@ -3,6 +3,7 @@ compulsory minimum, the paper's counting identities, plans that can actually run
 rules of the boundary that are decided before any device work."""
 import ctypes
 import itertools
+import math
 
 import pytest
 
@@ -319,7 +320,7 @@ MEASURED = [
     ((128, 384, 1536, 384), ff.DT_BF16, False, {(5, 64, 64, 32, 16, 2): 16.4, (1, 16, 64, 32, 24, 1): 10.8,
       (1, 32, 64, 32, 16, 1): 14.6, (5, 64, 64, 32, 32, 2): 16.1}),
     ((231, 512, 1024, 512), ff.DT_BF16, False, {(5, 128, 64, 32, 8, 2): 20.2, (1, 16, 64, 32, 8, 1): 12.5,
-      (1, 32, 64, 32, 8, 1): 15.2, (1, 16, 64, 32, 4, 1): 17.0}),
+      (1, 32, 64, 32, 8, 1): 15.2, (1, 16, 64, 32, 4, 1): 17.0, (1, 16, 64, 32, 16, 1): 12.1}),
     ((4, 7040, 15616, 7040), ff.DT_BF16, True, {(5, 32, 128, 32, 8, 1): 127.4, (5, 32, 128, 64, 16, 1): 149.5,
       (5, 32, 128, 32, 2, 1): 173.8}),
     ((126, 1920, 5136, 1920), ff.DT_F16, False, {(5, 64, 64, 32, 8, 2): 27.3, (5, 64, 64, 32, 16, 2): 28.2,
@@ -393,3 +394,29 @@ def test_fp32_predictions_against_measured_calls():
             t = ff.ffuse_traffic_model(p, ff.DT_F32, g, *shape).t_pred * 1e6
             print(shape, g, us, round(t, 1))
             assert us / 1.5 < t < 1.5 * us, (shape, g, us, t)
+
+
+# Small row blocks, bf16, us per call: (shape, gated, rows, ranges, us).  Two or fewer of each variant, drawn from the timings within
+# 12 % of their shape's best plan.
+SMALL_BLOCKS = [
+    ((87, 2296, 96, 144), False, 16, 2, 10.9), ((53, 456, 1984, 456), False, 16, 31, 10.1), ((34, 496, 72, 320), False, 16, 2, 6.6),
+    ((182, 768, 2048, 768), False, 16, 16, 20.2), ((58, 568, 4192, 920), False, 16, 32, 22.1), ((108, 1944, 544, 1944), False, 16, 9, 19.3),
+    ((14, 320, 352, 1632), False, 16, 6, 10.6), ((13, 1200, 1592, 72), False, 32, 25, 11.1), ((180, 328, 1872, 328), False, 32, 16, 13.7),
+    ((176, 520, 336, 144), True, 16, 6, 8.7), ((158, 384, 512, 384), True, 16, 8, 9.6), ((105, 512, 1536, 512), True, 16, 24, 12.3),
+    ((23, 448, 1480, 592), True, 16, 24, 11.8), ((68, 2152, 656, 760), True, 16, 11, 21.1), ((64, 1976, 192, 1800), True, 16, 3, 20.5),
+    ((128, 768, 2688, 128), True, 32, 32, 18.5), ((193, 512, 1408, 512), True, 32, 22, 16.5), ((36, 208, 1352, 208), False, 16, 22, 6.9),
+    ((10, 208, 2248, 208), False, 16, 32, 8.1), ((49, 72, 512, 288), False, 16, 8, 5.7), ((166, 128, 9968, 128), False, 32, 32, 14.9),
+    ((569, 200, 1408, 312), False, 32, 16, 14.3), ((118, 136, 752, 144), True, 16, 12, 6.7), ((893, 64, 80, 240), True, 16, 1, 5.2),
+    ((964, 64, 560, 400), True, 16, 4, 12.5), ((214, 128, 5632, 128), True, 32, 32, 14.6), ((2734, 96, 632, 352), True, 32, 2, 21.2),
+]
+
+
+def test_small_row_blocks_are_priced_as_they_run():
+    """Predictions scatter by 7 % round 2940 timings: 27 of them average within 3 % (two standard errors), each within three times
+    the scatter.  (The constants of the four-wave kernel are 5 % high here, 8 % over all.)"""
+    logs = []
+    for shape, gated, rows, ranges, us in SMALL_BLOCKS:
+        p = ff.make_plan(1, bm=rows, bh=64, bn2=256, bk=32, splits=ranges, h_level=1, raster=1)
+        logs.append(math.log(ff.ffuse_traffic_model(p, ff.DT_BF16, gated, *shape).t_pred * 1e6 / us))
+        assert abs(logs[-1]) <= 0.21, (shape, us, logs[-1])
+    assert abs(sum(logs) / len(logs)) <= 0.03, sum(logs) / len(logs)
