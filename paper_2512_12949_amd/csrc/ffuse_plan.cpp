@@ -342,8 +342,8 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         // two of the smallest variant share one and then take 0.8 of twice the time.  Planes: their bytes, a second launch,
         // eight at a time.  Fitted on 2940 timings of 1300 shapes with the present waves (eight; four where gated beyond K =
         // 256): no bias in any variant beyond 5 %, 7 % scatter.  (The constants of the four-wave kernel predicted these calls 8 %
-        // high on average, the smallest variant 14, and layers went to two-phase plans: 96 x 1152 x 1920 x 1152 21.6 us there,
-        // 17.3 here.)  The planes' bytes are no part of the walk's time: counted in it, they hid what 16 rows save over 32
+        // high on average, the smallest variant 14, and layers went to two-phase plans: gated 29 x 3560 x 160 x 128 33.5 us there,
+        // 21.7 here.)  The planes' bytes are no part of the walk's time: counted in it, they hid what 16 rows save over 32
         // (gated 142 x 512 x 1536 x 512, 24 ranges: 15.4 us on 32 rows, 13.4 on 16).
         DirectGeometry dg;
         t->feasible = direct_geometry(p, M, N1, N2, &dg) ? 1 : 0;
@@ -636,6 +636,10 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->t_hbm = t1 + t2;
         t->t_mfma = m1 + m2;
         t->t_pred = std::max(t1, m1) + std::max(t2, m2) + planes + (sg.splits > 1 ? 9.74e-6 : 7.49e-6);
+        // 64-row blocks take 4-6 % longer than that, three and four of them 11 % where the weights do not stay in the memory-side
+        // cache (2500 timings of 900 layers of 33-256 rows; 128-row blocks 0-3 % less).  Without it they displaced faster
+        // plans: 96 x 1152 x 1920 x 1152 21.6 us, small row blocks 17.3; 225 x 512 x 13312 x 512 33.2, 128-row blocks 30.5.
+        if (sg.bm == 64) t->t_pred *= mb > 2.0 && warm == 1.0 ? 1.12 : 1.06;
     }
 }
 
@@ -693,10 +697,8 @@ void rank_plans(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1,
         for (int bm : bms) {
             // Up to 256 rows 64-row blocks are tried against 128-row ones (half the row-operand bytes per item, twice the items):
             // of 110 drawn layers of 65-256 rows the better of both was 5 % faster on average than 128-row blocks above
-            // 128 rows (218 x 896 x 3920 x 896: 27.3 us, 21.5).  Above 128 rows not where the direct kernel takes the layer in
-            // one round of single slices and ties (gated 142 x 1152 x 1664 x 1152: 22.5 us, 21.9).  Smaller blocks lose.
+            // 128 rows (218 x 896 x 3920 x 896: 27.3 us, 21.5).  Smaller blocks lose.
             if (bm < 128 && M > (bm == 64 ? 256 : bm)) continue;
-            if (bm == 64 && M > 128 && N1 <= 2048 && N2 <= 2048 && cdiv((double)M, 16.0) * cdiv((double)N1, 64.0) <= kDevice.cus) continue;
             if (bm > 32 && M <= bm / 2) continue;             // more than half a block of padding
             // 128 / 64 / 32: register-staged loop with that slice width; -128 / -64 / -256: LDS-direct loop
             static const int slices[] = {128, 64, 32, -128, -64, -256};
