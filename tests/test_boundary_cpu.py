@@ -1,6 +1,7 @@
 """C-ABI boundary checks that need no GPU: the library loads, exports every symbol the
 header declares, and rejects bad arguments before touching the device."""
 import ctypes
+import itertools
 import os
 import re
 
@@ -233,6 +234,14 @@ def test_group_local_barrier_condition_of_256_column_slices_in_128_row_blocks():
         assert got == _independent(M, N1, N2, 128, 128 if gated else 256, splits, raster), (M, K, N1, N2, gated, splits, raster)
         seen.add(got)
     assert seen == {True, False}
+
+
+def test_group_local_barrier_condition_of_three_row_blocks_in_one_patch():
+    for M, K, N1, N2 in ((129, 264, 4104, 1032), (192, 1216, 10096, 1216), (150, 512, 5248, 2048), (160, 64, 520, 72), (192, 4096, 11008, 4096)):
+        for gated, bh, splits in itertools.product((False, True), (64, 128), (2, 4, 8, 16)):
+            plan = ff.make_plan(ff.FAMILY_TWOPHASE, bm=64, bh=bh, bn2=256, bk=32, splits=splits, raster=3)
+            want = _independent(M, N1, N2, 64, bh, splits, 3)
+            assert ff.ffuse_plan_group_local(plan, ff.DT_BF16, gated, M, K, N1, N2) == want, (M, K, N1, N2, gated, bh, splits)
 
 
 def test_group_local_barrier_condition_matches_the_item_maps():

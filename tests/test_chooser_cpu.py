@@ -331,7 +331,8 @@ MEASURED = [
     ((128, 4096, 11008, 4096), ff.DT_BF16, True, {(5, 64, 128, 32, 8, 2): 90.3, (5, 128, 64, 32, 16, 1): 87.4,
       (5, 64, 128, 32, 32, 2): 108.6, (5, 64, 128, 32, 2, 2): 128.1}),
     ((142, 1152, 1664, 1152), ff.DT_BF16, True, {(5, 128, 64, 32, 8, 2): 28.4, (1, 16, 64, 32, 26, 1): 23.3,
-      (5, 128, 128, 32, 16, 2): 32.5, (5, 128, 64, 64, 8, 2): 34.0, (5, 64, 64, 32, 8, 2): 23.2}),
+      (5, 128, 128, 32, 16, 2): 32.5, (5, 128, 64, 64, 8, 2): 34.0, (5, 64, 64, 32, 8, 2): 23.2,
+      (5, 64, 64, 32, 8, 3): 22.6}),
 ]
 
 
@@ -434,6 +435,15 @@ MEASURED_64 = [
       (1, 16, 64, 32, 16, 1): 24.6}),
     ((128, 984, 2768, 984), False, {(1, 16, 64, 32, 32, 1): 20.0, (5, 64, 64, 32, 8, 2): 22.4, (5, 64, 64, 32, 8, 1): 22.9,
       (5, 64, 64, 32, 16, 2): 22.9, (5, 64, 128, 32, 8, 2): 23.2}),
+    # three row blocks: one patch of weight slices for all of them
+    ((192, 1216, 10096, 1216), True, {(5, 64, 128, 32, 16, 3): 34.5, (5, 128, 128, 32, 16, 2): 39.7, (5, 64, 64, 32, 16, 3): 39.8,
+      (5, 64, 128, 32, 16, 2): 42.4, (5, 128, 128, 32, 16, 1): 42.5}),
+    ((141, 1664, 5248, 1664), True, {(5, 64, 64, 32, 8, 3): 29.4, (5, 64, 128, 32, 8, 3): 32.6, (5, 64, 128, 32, 8, 2): 33.6,
+      (5, 64, 64, 32, 8, 2): 34.7, (5, 128, 64, 32, 16, 2): 35.7}),
+    ((131, 2568, 4448, 2568), True, {(5, 64, 64, 32, 4, 3): 38.7, (5, 128, 64, 32, 8, 2): 43.3, (5, 64, 64, 32, 4, 2): 43.5,
+      (5, 64, 64, 32, 16, 2): 45.8, (5, 64, 64, 32, 4, 1): 45.9}),
+    ((152, 984, 8720, 2472), False, {(5, 64, 128, 32, 8, 3): 33.8, (5, 64, 128, 32, 8, 2): 36.5, (5, 64, 64, 32, 8, 3): 37.0,
+      (5, 128, 128, 32, 8, 2): 37.1}),
 ]
 
 
