@@ -601,7 +601,12 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         const double share = std::pow(std::min(mb, 4.0), 0.84);
         const auto streams = [&](double n) { return sg.bm == 256 ? std::min(n, (double)d.cus) : n / cdiv(n, d.cus) / share; };
         const double t1 = copies * b1 / std::min(warm * d.hbm_bw, streams(items1) * per_wg1) + re1 / d.fabric_bw + per_item * cdiv(items1, d.cus);
-        const double t2 = copies * b2 / std::min(warm * d.hbm_bw, streams(items) * per_wg2) + re2 / d.fabric_bw + per_item2 * cdiv(items, d.cus);
+        // The second phase writes its planes while it streams W2, and they count as its bytes: with W2 alone twice the ranges
+        // looked the better where they fill the CUs (gated 128 x 4096 x 11008 x 4096, 8 and 16 ranges: second phase 26 and 21 us,
+        // the call 87.8 and 89.3, on weights called again 77.7 and 86.3; 128 x 2048 x 8192 x 2048 32.0 and 35.2).
+        const double written = sg.splits > 1 ? 4.0 * m * n2 * sg.splits : 0.0;
+        const double t2 = std::max(copies * b2 / (streams(items) * per_wg2), (copies * b2 + written) / (warm * d.hbm_bw)) +
+                          re2 / d.fabric_bw + per_item2 * cdiv(items, d.cus);
         // planes are written and read once; small transfers reach about half the cache rate
         const double planes = sg.splits > 1 ? 2.0 * 4.0 * m * n2 * sg.splits / (0.615 * d.fabric_bw) : 0.0;
         // matrix-core time of each phase: items run one per CU, at the block GEMM's efficiency
