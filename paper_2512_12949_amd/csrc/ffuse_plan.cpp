@@ -337,27 +337,31 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
 
     if (is_direct(p)) {
         // A slice of 64 hidden columns costs two barriers and the issue of its loads: up to K = 256 0.72 us + 3.0 ns per k and
-        // 0.27 for a second block of 256 output columns (gated 1.45 of that; 32 rows 1.56); beyond, 1.21 us per turn of the
-        // operand ring (512 k, gated 256: 1.26) and 0.52 per block of output columns (32 rows 1.31).  Workgroups run one per CU;
+        // 0.28 for a second block of 256 output columns (gated 1.44 of that; 32 rows 1.56); beyond, 1.21 us per turn of the
+        // operand ring (512 k, gated 256: 1.26) and 0.51 per block of output columns (32 rows 1.31).  Workgroups run one per CU;
         // two of the smallest variant share one and then take 0.8 of twice the time.  Planes: their bytes, a second launch,
-        // eight at a time.  Fitted on 2940 timings of 1300 shapes with the present waves (eight; four where gated beyond K =
+        // eight at a time.  Fitted on 3600 timings of 1800 shapes with the present waves (eight; four where gated beyond K =
         // 256): no bias in any variant beyond 5 %, 7 % scatter.  (The constants of the four-wave kernel predicted these calls 8 %
         // high on average, the smallest variant 14, and layers went to two-phase plans: gated 29 x 3560 x 160 x 128 33.5 us there,
         // 21.7 here.)  The planes' bytes are no part of the walk's time: counted in it, they hid what 16 rows save over 32
         // (gated 142 x 512 x 1536 x 512, 24 ranges: 15.4 us on 32 rows, 13.4 on 16).
+        // Workgroups go round the eight XCDs range by range: with a multiple of eight ranges an XCD fills its L2 with its own
+        // eighth of the weights, with an odd number every XCD reads them all.  Those fills come at 6.2 TB/s (gated 148 x 1144 x 3192 x
+        // 128, 25 ranges: predicted 21 us at one rate for every count, measured 37, two-phase 25).
         DirectGeometry dg;
         t->feasible = direct_geometry(p, M, N1, N2, &dg) ? 1 : 0;
         if (!t->feasible) return;
         const double mb = cdiv(m, dg.bm), wgs = mb * dg.ranges;
         const bool shortk = K <= 256 && dg.ng <= 2, tall = dg.bm == 32;
-        const double slice = 1e-6 * (shortk ? (0.717 + 0.003 * k + 0.268 * (dg.ng - 1)) * (gated ? 1.446 : 1.0) * (tall ? 1.562 : 1.0)
-                                            : (0.367 + (gated ? 1.262 * cdiv(k, 256.0) : 1.214 * cdiv(k, 512.0)) + 0.522 * dg.ng) * (tall ? 1.307 : 1.0));
+        const double slice = 1e-6 * (shortk ? (0.717 + 0.003 * k + 0.278 * (dg.ng - 1)) * (gated ? 1.44 : 1.0) * (tall ? 1.56 : 1.0)
+                                            : (0.391 + (gated ? 1.262 * cdiv(k, 256.0) : 1.208 * cdiv(k, 512.0)) + 0.513 * dg.ng) * (tall ? 1.306 : 1.0));
         double rounds = cdiv(wgs, d.cus);
         if (shortk && dg.ng == 1 && rounds > 1.0) rounds *= 0.8;
         const double weights = e * (g * k * n1 + n1 * n2), planes = dg.ranges > 1 ? 2.0 * 4.0 * m * n2 * dg.ranges : 0.0;
         t->workgroups = (int)std::min(wgs, (double)d.cus);
         t->l2_bytes = mb * weights + e * m * k * dg.ranges;
-        t->fabric_bytes = std::min(8.0, mb) * weights + e * m * k * std::min(8, dg.ranges) + e * m * n2 + planes;
+        const double fills = std::min(mb, dg.ranges % 8 == 0 ? 1.0 : dg.ranges % 4 == 0 ? 2.0 : dg.ranges % 2 == 0 ? 4.0 : 8.0);
+        t->fabric_bytes = fills * weights + e * m * k * std::min(8, dg.ranges) + e * m * n2 + planes;
         t->reduce_bytes = planes;
         t->hbm_bytes = t->q_min;
         const int waves = direct_waves(gated, shortk, dg.bm, dg.ng, dg.slices, wgs > d.cus);
@@ -368,8 +372,8 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         t->t_fabric = t->fabric_bytes / d.fabric_bw;
         t->t_l2 = t->l2_bytes / d.l2_bw;
         t->t_mfma = rounds * dg.slices * slice;
-        t->t_reduce = dg.ranges > 1 ? planes / (0.413 * d.fabric_bw) + 1.46e-6 + 0.501e-6 * cdiv(dg.ranges, 8.0) : 0.0;
-        t->t_pred = 2.39e-6 + std::max({t->t_mfma, t->t_hbm, (t->fabric_bytes - planes) / d.fabric_bw}) + t->t_reduce;
+        t->t_reduce = dg.ranges > 1 ? planes / (0.413 * d.fabric_bw) + 1.49e-6 + 0.495e-6 * cdiv(dg.ranges, 8.0) : 0.0;
+        t->t_pred = 2.38e-6 + std::max({t->t_mfma, t->t_hbm, (t->fabric_bytes - planes) / 6.2e12}) + t->t_reduce;
         return;
     }
     if (p.family == FFUSE_FAMILY_REDUCE) {

@@ -465,3 +465,19 @@ def test_planes_are_bytes_of_the_second_phase(shape, gated, plans):
     c = ff.ffuse_choose_plan(ff.DT_BF16, 3 if gated else 2, gated, *shape)
     key = (c.family, c.bm, c.bh, c.bk, c.splits, c.raster)
     assert key in plans and plans[key] == min(plans.values()), (key, plans)
+
+
+def test_small_row_blocks_fill_each_l2_with_what_its_ranges_read():
+    """Workgroups go round the XCDs range by range: eight ranges read an eighth of the weights each, 25 all of them."""
+    shape = (148, 1144, 3192, 128)
+    weights = 2 * (2 * 1144 * 3192 + 3192 * 128)
+    fabric = {}
+    for ranges in (8, 10, 13, 25):   # of 50 slices: all of them are kept
+        p = ff.make_plan(1, bm=16, bh=64, bn2=256, bk=32, splits=ranges, h_level=1, raster=1)
+        t = ff.ffuse_traffic_model(p, ff.DT_BF16, True, *shape)
+        fabric[ranges] = (t.fabric_bytes - t.reduce_bytes) / weights
+    # (ranges of 7, 5, 4 and 2 slices: 8, 10, 13 and 25 of them)
+    assert fabric[8] < 1.2 and 4.0 <= fabric[10] < 4.3 and 8.0 <= fabric[13] < 8.3 and 8.0 <= fabric[25] < 8.3, fabric
+    # where every XCD reads all of it, the layer is better off in the two-phase kernel: 25.0 us
+    c = ff.ffuse_choose_plan(ff.DT_BF16, 3, True, *shape)
+    assert c.family == ff.FAMILY_TWOPHASE, c.as_dict()
