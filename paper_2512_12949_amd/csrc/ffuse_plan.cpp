@@ -523,8 +523,8 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         // weights through its load path, as long as the chunk's matrix instructions take.  Fitted on the device
         // (row-block rounds x (chunks x chunk time + a fixed part per row block)): the fraction of the matrix peak
         // a chunk sustains grows with its size -- kRowsEffSmall for K = N2 = 512 (8.4 Mflop per chunk: 32768 x 512 x 4096 x 512
-        // in 368 us), kRowsEff for K = N2 = 1024 (16.8 Mflop: 32768 x 1024 x 8192 x 1024 in 1056 us, x 1024 x 1024 in
-        // 170) -- and every row block pays about 20 us on top (X into registers, the ring primed again after the
+        // in 368 us), kRowsEff for K = N2 = 1024 (16.8 Mflop: 32768 x 1024 x 8192 x 1024 in 1056 us, 1040-1190 by the
+        // chip's temperature, x 1024 x 1024 in 170) -- and every row block pays about 20 us on top (X into registers, the ring primed again after the
         // output stores, the output block stored; the first one also the kernel's start: 120 KB of LDS, a long
         // unrolled loop to fetch), which is why the family loses to every other on problems of a few row blocks.
         RowsGeometry rg;
@@ -568,9 +568,9 @@ void traffic_model(const ffuse_plan_t& p, int dtype, int gated, int64_t M, int64
         // weight slice is fetched once per XCD patch of `raster` row blocks: the first fetch
         // comes from HBM, repeats (and the rows, once per slice group) from the Infinity Cache.
         // Fixed: launch and barrier 7.5 us, and 2.25 for the launch that sums the planes.
-        // The constants of this model and of the small row blocks' were fitted together on every plan of 4707 measured
-        // shapes (FFN 1-32768 rows, widths 128-8192, and 3x3 chains; 30 plans each): the plan ranked first is 0.5 % behind
-        // the best measured one on average; predictions of plans worth running average 2 % high and scatter by 8 %.
+        // The constants of this model were fitted with the small row blocks' (those again since, see there) on every plan of 4707
+        // measured shapes (FFN 1-32768 rows, widths 128-8192, and 3x3 chains; 30 plans each): the plan ranked first was 0.5 %
+        // behind the best measured one on average; predictions of plans worth running averaged 2 % high and scattered by 8 %.
         TwoPhaseGeometry sg;
         two_phase_geometry(p, gated, M, N1, N2, &sg);
         const double bh1 = sg.bh1;
@@ -812,7 +812,8 @@ bool choose_plan(int dtype, int act, int gated, int64_t M, int64_t K, int64_t N1
     *out = r.front().plan;
     if (objective != FFUSE_OBJECTIVE_BYTES) {
         // time objective: a near-tie goes to the schedule that keeps the intermediate on the chip -- a rows plan predicted
-        // within 6 % of the fastest whose bytes between the L2s and the fabric are at most half of its.  (Between plans
+        // within 6 % of the fastest whose bytes between the L2s and the fabric are at most half of its.  (It costs time: 32768 x 1024 x
+        // 8192 x 1024 fp16, predicted 5 % apart, 1045 us against 998 and 1075 against 1006 in turn on one card, and more as it warms.)  (Between plans
         // of one family the prediction already counts those bytes; among them the rule took gated 4023 x 256 x 1080 x 256 from
         // 128- to 256-row tiles, 34 -> 47 us.)
         ffuse_traffic_t tb;

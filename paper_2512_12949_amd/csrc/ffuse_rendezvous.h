@@ -33,7 +33,8 @@ __device__ __forceinline__ bool map_item(int MB, int S, int raster, int xcd, int
 // isolation, waiting for all eight: 1.8-3.9 us, against 3.8-6.5
 // with a returning add plus a second, group-to-global add, and 7-12.5 with a releasing add.
 // Bounded: on expiry the error word is set and every workgroup leaves (returns false).
-// `between` runs after the arrival and before the wait (loads that may be issued early).
+// `between` runs after the arrival and before the wait, in every wave (loads that may be issued early: the poll returns behind
+// those of its own wave, so the LDS-direct kernels leave them to the other waves; the streaming kernel's go out in all).
 template <class Between>
 __device__ __forceinline__ bool two_phase_rendezvous(const TwoPhaseArgs& a, volatile uint32_t& verdict, int tid, int xcd, int GX,
                                                      uint32_t wait, uint32_t round, Between&& between) {

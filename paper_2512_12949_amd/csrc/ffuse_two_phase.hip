@@ -74,10 +74,10 @@ template <typename T, bool GATED> struct TwoPhaseGemms<T, GATED, 128, false, 128
     static constexpr bool DEEP = true;
     static constexpr bool PREFETCH = true;
 };
-// 256-column slices: the wave tile of the second phase (64 x 128) in the first one as well.  With 128 x 128
-// items a wave reads 2 fragments per MFMA pair and the phase is bound by LDS reads (0.36 of the MFMA peak);
-// 64 x 128 wave tiles sustain 0.46.  512 x 4096 x 16384 x 4096: 256 items, one full round instead of two,
-// 163 -> 145 us.  (Gated 128-column slices already are this tile.)
+// 256-column slices: the tile of the second phase in the first one as well, 64 x 64 to each of eight waves.  512 x 4096 x 16384 x
+// 4096: 256 items, one full round instead of two of 128 columns, 163 -> 145 us (with four waves of 64 x 128, which read 1.5
+// fragments per MFMA pair instead of 2 and sustain 0.46 of the MFMA peak instead of 0.36 in long calls; with eight 141-143, the matrix
+// pipes 0.51 busy at 1.8 GHz).  Gated 128-column slices have this much work per item already, 32 x 64 of each branch to a wave.
 template <typename T> struct TwoPhaseGemms<T, false, 128, false, 256, true> {
     static constexpr int BH1 = 256, WAVES = 8;
     template <bool NT> using G1 = WideGemm<T, false, 128, 256, 2, WAVES / 2, 4, NT>;
