@@ -413,7 +413,7 @@ SMALL_BLOCKS = [
 
 
 def test_small_row_blocks_are_priced_as_they_run():
-    """Predictions scatter by 7 % round 2940 timings: 27 of them average within 3 % (two standard errors), each within three times
+    """Predictions scatter by 7 % round 3600 timings: 27 of them average within 3 % (two standard errors), each within three times
     the scatter.  (The constants of the four-wave kernel are 5 % high here, 8 % over all.)"""
     logs = []
     for shape, gated, rows, ranges, us in SMALL_BLOCKS:
